@@ -15,9 +15,13 @@ conditions of the paper:
 
 The 2D stencil is symmetric under x -> -x and y -> -y, so the maps
 decouple by the parity class (a mod 2, b mod 2) of the monomial xi^a eta^b
-once the stencil data are combined into even/odd sums and differences.  The
-generator applies that change of variables exactly and emits only the
-non-zero entries, which roughly halves the arithmetic.
+once the stencil data are combined into even/odd sums and differences, and
+the (even, even) class once more under the exchange of x and y.  The
+generator applies these changes of variables exactly and emits only the
+non-zero entries, which roughly halves the arithmetic.  The coefficients are
+kept in twice the cell's reference coordinates, where the outer
+Gauss-Lobatto nodes are +-1 and the inner ones +-1/sqrt(5): the evaluation
+then needs two constants and is factored axis by axis.
 
 Output: straight-line FP64 device code with each constant written as an
 exact hexadecimal literal of the correctly rounded double.
@@ -27,6 +31,7 @@ Run:  python gen_recon.py > recon_gen.h
 from __future__ import annotations
 
 import itertools
+import re
 import sys
 from fractions import Fraction
 
@@ -302,10 +307,6 @@ def emit_2d(lines):
         cvars[name] = sp.Symbol(name)
         cdefs.append((name, expr_c))
         raw[name] = sym_expr
-    # u combos
-    for dy in (-1, 0, 1):
-        pass
-    # explicit: x-stage per row
     def u_(dx, dy):
         return f"u[{lab(dx, dy) - 1}]"
     def v_(dx, dy):
@@ -316,16 +317,12 @@ def emit_2d(lines):
     for dy, tag in ((-1, "b"), (0, "m"), (1, "t")):
         add(f"ue{tag}", f"{u_(-1, dy)} + {u_(1, dy)}", U[lab(-1, dy) - 1] + U[lab(1, dy) - 1])
         add(f"uo{tag}", f"{u_(1, dy)} - {u_(-1, dy)}", U[lab(1, dy) - 1] - U[lab(-1, dy) - 1])
-    comb = []
-    # y-stage
-    def ystage(prefix, cen):
-        # cen: dict tag->(cexpr, symexpr) for rows b,m,t
-        pass
+    add("usm", f"{u_(0, -1)} + {u_(0, 1)}", U[lab(0, -1) - 1] + U[lab(0, 1) - 1])
     U5 = U[4]
     final_u = {
         "a00": (f"{u_(0, 0)}", U5),
-        "a01": (f"{u_(0, -1)} + {u_(0, 1)}", U[lab(0, -1) - 1] + U[lab(0, 1) - 1]),
-        "a02": ("uem", raw["uem"]),
+        "a01": ("usm + uem", raw["usm"] + raw["uem"]),
+        "a02": ("usm - uem", raw["usm"] - raw["uem"]),
         "a03": ("ueb + uet", raw["ueb"] + raw["uet"]),
         "a10": ("uom", raw["uom"]),
         "a11": ("uob + uot", raw["uob"] + raw["uot"]),
@@ -339,8 +336,6 @@ def emit_2d(lines):
         add(f"vs{tag}", f"{v_(1, dy)} + {v_(-1, dy)}", V[lab(1, dy) - 1] + V[lab(-1, dy) - 1])
         add(f"vd{tag}", f"{v_(1, dy)} - {v_(-1, dy)}", V[lab(1, dy) - 1] - V[lab(-1, dy) - 1])
     final_v = {
-        "b00": ("vdm", raw["vdm"]),                         # (0,0)
-        "b01": ("vdb + vdt", raw["vdb"] + raw["vdt"]),      # (0,0)
         "b10": ("vsm", raw["vsm"]),                         # (1,0)
         "b11": ("vsb + vst", raw["vsb"] + raw["vst"]),      # (1,0)
         "b12": (f"{v_(0, 0)}", V[4]),                       # (1,0)
@@ -352,14 +347,21 @@ def emit_2d(lines):
         add(f"ws{tag}", f"{w_(dx, 1)} + {w_(dx, -1)}", W[lab(dx, 1) - 1] + W[lab(dx, -1) - 1])
         add(f"wd{tag}", f"{w_(dx, 1)} - {w_(dx, -1)}", W[lab(dx, 1) - 1] - W[lab(dx, -1) - 1])
     final_w = {
-        "c00": ("wdm", raw["wdm"]),                         # (0,0)
-        "c01": ("wdl + wdr", raw["wdl"] + raw["wdr"]),      # (0,0)
         "c20": ("wsm", raw["wsm"]),                         # (0,1)
         "c21": ("wsl + wsr", raw["wsl"] + raw["wsr"]),      # (0,1)
         "c22": (f"{w_(0, 0)}", W[4]),                       # (0,1)
         "c10": ("wdr - wdl", raw["wdr"] - raw["wdl"]),      # (1,0)
         "c30": ("wsr - wsl", raw["wsr"] - raw["wsl"]),      # (1,1)
     }
+    # (0,0) from both: sums and differences under the exchange of x and y
+    add("vds", "vdb + vdt", raw["vdb"] + raw["vdt"])
+    add("wds", "wdl + wdr", raw["wdl"] + raw["wdr"])
+    final_w.update({
+        "b00": ("vdm + wdm", raw["vdm"] + raw["wdm"]),
+        "b01": ("vds + wds", raw["vds"] + raw["wds"]),
+        "c00": ("vdm - wdm", raw["vdm"] - raw["wdm"]),
+        "c01": ("vds - wds", raw["vds"] - raw["wds"]),
+    })
     finals = {}
     finals.update(final_u)
     finals.update(final_v)
@@ -375,7 +377,12 @@ def emit_2d(lines):
     lines.append("/* ---- 2D: q_2 (6 coefs), q_3 (10), q_4 (21) of eqs. (2D-q2)-(2D-q4),")
     lines.append("   centre average exact, other conditions in the least-squares sense.")
     lines.append("   Monomial order: degree by degree, xi power descending:")
-    lines.append("   " + ", ".join(f"x^{a}y^{b}" for a, b in MON) + " */")
+    lines.append("   " + ", ".join(f"x^{a}y^{b}" for a, b in MON) + ".")
+    lines.append("   With c the monomial coefficients, entry (a, b) holds 2^(1-a-b) c_ab (the")
+    lines.append("   coefficients in X = 2 xi, Y = 2 eta, twice over, so that the outer nodes are")
+    lines.append("   +-1); entries 3 and 5 hold the sum and 2/5 of the difference of the x^2 and")
+    lines.append("   y^2 coefficients, entries 10 and 14 the sum and 12/25 of the difference of")
+    lines.append("   the x^4 and y^4 ones (the exchange x <-> y decouples them) */")
     lines.append("MR_DEV inline void mr2_maps(const double u[9], const double v[9], const double w[9],")
     lines.append("                            double q2[6], double q3[10], double q4[21]) {")
     for name, cexpr in cdefs:
@@ -383,9 +390,25 @@ def emit_2d(lines):
     for n in fin_names:
         cexpr = finals[n][0]
         lines.append(f"  const double {n} = {cexpr};")
+    # basis of the coefficients: z = B c
+    B = sp.zeros(21, 21)
+    for p, (a, b) in enumerate(MON):
+        B[p, p] = R(2) ** (1 - a - b)
+    for p, q, f in ((3, 5, R(2, 5)), (10, 14, R(12, 25))):
+        sp_, sq_ = B[p, p], B[q, q]
+        B[p, q] = sq_
+        B[q, p], B[q, q] = f * sp_, -f * sq_
+    Bi = B.inv()
+    zcls = {p: (MON[p][0] % 2, MON[p][1] % 2, 1 if p in (5, 14) else 0) for p in range(21)}
     total_terms = 0
+    rows2 = None
     for l, arr in ((2, "q2"), (3, "q3"), (4, "q4")):
-        M = lsq_map_2d(nco[l], conds[l])
+        M = B[:nco[l], :nco[l]] * lsq_map_2d(nco[l], conds[l])
+        # q_2 and q_3 share these entries (the evaluation takes q_3's)
+        if l == 2:
+            rows2 = M
+        elif l == 3:
+            assert all(M[p, :9] == rows2[p, :9] and not any(M[p, 9:]) for p in (0, 3, 4, 5))
         datas = [dsym(t, lb) for t, lb in conds[l]]
         for p in range(nco[l]):
             expr = sum(M[p, k] * datas[k] for k in range(len(datas)))
@@ -418,11 +441,11 @@ def emit_2d(lines):
                                     * mono_avg(a1 + a2 - 2 * ax, 0) * mono_avg(b1 + b2 - 2 * ay, 0))
         return G
     for kappa, n, nm in ((2, 6, "mr2_beta_k2"), (3, 10, "mr2_beta_k3"), (5, 21, "mr2_beta_k5")):
-        G = gram2(kappa, n)
+        G = Bi[:n, :n].T * gram2(kappa, n) * Bi[:n, :n]
         lines.append(f"MR_DEV inline double {nm}(const double c[{n}]) {{")
         lines.append("  double b = 0.0, part;")
-        for cls in ((0, 0), (1, 0), (0, 1), (1, 1)):
-            idx = [p for p in range(1, n) if (MON[p][0] % 2, MON[p][1] % 2) == cls]
+        for cls in ((0, 0, 0), (0, 0, 1), (1, 0, 0), (0, 1, 0), (1, 1, 0)):
+            idx = [p for p in range(1, n) if zcls[p] == cls]
             # check block structure
             for p in idx:
                 for s in range(1, n):
@@ -436,32 +459,76 @@ def emit_2d(lines):
         lines.append("}")
 
     # ---- evaluation at the 4x4 Gauss-Lobatto grid ----
-    s5 = sp.sqrt(5) / 10
-    absn = [R(1, 2), s5]      # |node| for k = 0/3 and 1/2
-    lines.append("/* values of a degree-5 polynomial at (xi_k, eta_l), out[k + 4 l],")
-    lines.append("   xi, eta in {-1/2, -sqrt(5)/10, sqrt(5)/10, 1/2} */")
+    # nodes X = -1, -sigma, sigma, 1 with sigma = 1/sqrt(5), t = sigma^2 = 1/5
+    t, sg = R(1, 5), 1 / sp.sqrt(5)
+    T, S = lit(t), lit(sg)
+    E = []
+    # even-even class at (|X|, |Y|) = (1, 1), (1, s), (s, 1), (s, s)
+    E += ["h = c[10] + c[12]", "e00 = c[0] + (c[3] + h)", f"e11 = c[0] + {T} * (c[3] + {T} * h)",
+          f"em = c[0] + {lit((1 + t) / 2)} * c[3] + {lit((1 + t * t) / 2)} * c[10] + {T} * c[12]",
+          "ed = c[5] + c[14]", "e01 = em + ed", "e10 = em - ed"]
+    # odd classes without the factors X, Y, X Y: x<i><j> at |X|_i, |Y|_j
+    for n_, (k1, k3, k12, k5, k32, k14) in (("x", (1, 6, 8, 15, 17, 19)), ("y", (2, 9, 7, 20, 18, 16))):
+        E += [f"{n_}a = c[{k1}] + c[{k3}] + c[{k5}]", f"{n_}b = c[{k1}] + {T} * (c[{k3}] + {T} * c[{k5}])",
+              f"{n_}c = c[{k12}] + c[{k32}]", f"{n_}d = c[{k12}] + {T} * c[{k32}]"]
+        # own axis at 1 / s (first index), the other axis at 1 / s (second)
+        E += [f"{n_}00 = {n_}a + ({n_}c + c[{k14}])", f"{n_}01 = {n_}a + {T} * ({n_}c + {T} * c[{k14}])",
+              f"{n_}10 = {n_}b + ({n_}d + c[{k14}])", f"{n_}11 = {n_}b + {T} * ({n_}d + {T} * c[{k14}])"]
+    E += ["g = c[11] + c[13]", "r00 = c[4] + g", f"r11 = c[4] + {T} * g", f"r01 = c[4] + c[11] + {T} * c[13]",
+          f"r10 = c[4] + c[13] + {T} * c[11]"]
+    lines.append("/* values of the polynomial (2D basis above; half the sum of the entries times")
+    lines.append("   the monomials in X, Y: the factor 1/2 belongs to the caller's weights) at")
+    lines.append("   (xi_k, eta_l), out[k + 4 l], xi, eta in {-1/2, -sqrt(5)/10, sqrt(5)/10, 1/2} */")
     lines.append("MR_DEV inline void mr2_eval(const double c[21], double out[16]) {")
-    # class values at |xi| = A/B, |eta| = A/B
-    for ix, X in enumerate(absn):
-        for iy, Y in enumerate(absn):
-            for cls in ((0, 0), (1, 0), (0, 1), (1, 1)):
-                terms = []
-                for p, (a, b) in enumerate(MON):
-                    if (a % 2, b % 2) == cls:
-                        terms.append((sp.nsimplify(X ** a * Y ** b), f"c[{p}]"))
-                lines.append(f"  const double P{cls[0]}{cls[1]}_{ix}{iy} = {dot_code(terms)};")
-    # node index k: 0 -> -A, 1 -> -B, 2 -> +B, 3 -> +A  (A = 1/2 -> ix 0, B -> ix 1)
-    node = {0: (0, -1), 1: (1, -1), 2: (1, 1), 3: (0, 1)}
+    for e in E:
+        lines.append(f"  const double {e};")
+    O = []
+    for ix in (0, 1):
+        for iy in (0, 1):
+            q, x, y, r = f"e{ix}{iy}", f"x{ix}{iy}", f"y{iy}{ix}", f"r{ix}{iy}"
+            f = {(0, 0): "1", (0, 1): S, (1, 0): S, (1, 1): T}[(ix, iy)]
+            if f == "1":
+                O += [f"s1_{ix}{iy} = {q} + {r}", f"d1_{ix}{iy} = {q} - {r}"]
+            else:
+                O += [f"s1_{ix}{iy} = fma({f}, {r}, {q})", f"d1_{ix}{iy} = fma(-{f}, {r}, {q})"]
+            if ix == iy:
+                O += [f"s2_{ix}{iy} = {x} + {y}", f"d2_{ix}{iy} = {x} - {y}"]
+            elif iy == 1:
+                O += [f"s2_{ix}{iy} = fma({S}, {y}, {x})", f"d2_{ix}{iy} = fma(-{S}, {y}, {x})"]
+            else:
+                O += [f"s2_{ix}{iy} = fma({S}, {x}, {y})", f"d2_{ix}{iy} = fma({S}, {x}, -{y})"]
+            kp, km = (3, 0) if ix == 0 else (2, 1)
+            lp, lm = (3, 0) if iy == 0 else (2, 1)
+            w = "" if ix == 0 or iy == 0 else S
+            for k, l, a, sgn, b in ((km, lm, "s1", "-", "s2"), (kp, lm, "d1", "+", "d2"), (km, lp, "d1", "-", "d2"),
+                                    (kp, lp, "s1", "+", "s2")):
+                if w:
+                    O += [f"out[{k + 4 * l}] = fma({'-' if sgn == '-' else ''}{w}, {b}_{ix}{iy}, {a}_{ix}{iy})"]
+                else:
+                    O += [f"out[{k + 4 * l}] = {a}_{ix}{iy} {sgn} {b}_{ix}{iy}"]
+    for o in O:
+        lines.append(f"  {'' if o.startswith('out') else 'const double '}{o};")
+    lines.append("}")
+    check_eval(E, O, B)
+
+
+def check_eval(E, O, B):
+    """The emitted evaluation statements against the monomials (60 digits)."""
+    ns = {"MR_KT": lambda i: sp.Float(_KTAB[i], 60), "fma": lambda a, b, c: a * b + c, "c": [], "out": [None] * 16}
+    coef = [sp.Rational(3 * p * p - 7 * p + 5, 11 + p) for p in range(21)]
+    ns["c"] = list(B * sp.Matrix(coef))
+    for st in E + O:
+        name, ex = st.split(" = ", 1)
+        ex = re.sub(r"-?0x1\.[0-9a-f]+p[+-][0-9]+", lambda m: repr(float.fromhex(m.group(0))), ex)
+        if name.startswith("out["):
+            ns["out"][int(name[4:-1])] = eval(ex, {}, ns)
+        else:
+            ns[name] = eval(ex, {}, ns)
+    nd = [-R(1, 2), -sp.sqrt(5) / 10, sp.sqrt(5) / 10, R(1, 2)]
     for l in range(4):
         for k in range(4):
-            ix, sx = node[k]
-            iy, sy = node[l]
-            t = f"P00_{ix}{iy}"
-            t += (" + " if sx > 0 else " - ") + f"P10_{ix}{iy}"
-            t += (" + " if sy > 0 else " - ") + f"P01_{ix}{iy}"
-            t += (" + " if sx * sy > 0 else " - ") + f"P11_{ix}{iy}"
-            lines.append(f"  out[{k + 4 * l}] = {t};")
-    lines.append("}")
+            want = sum(c * nd[k] ** a * nd[l] ** b for c, (a, b) in zip(coef, MON))
+            assert abs(sp.N(ns["out"][k + 4 * l] / 2 - want, 40)) < 1e-13, (k, l)
 
 
 def emit_mod(lines):

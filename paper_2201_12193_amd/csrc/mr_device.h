@@ -195,30 +195,35 @@ MR_HD void mr_recon2d(const double u[9], const double v[9], const double w[9],
     b4 = mr2_beta_k5(q4);
   } else {
     double p2[6], p3[10], p4[21];
-    for (int k = 0; k < 6; ++k) p2[k] = W.sg[1] * q2[k] - (k == 0 ? W.sgn[0] * u[4] : 0.0);
+    for (int k = 0; k < 6; ++k) p2[k] = W.sg[1] * q2[k];   /* q_1 has entry 0 only, which no beta reads */
     for (int k = 0; k < 10; ++k) p3[k] = W.sg[2] * q3[k] - (k < 6 ? W.sgn[1] * q2[k] : 0.0);
     for (int k = 0; k < 21; ++k) p4[k] = W.sg[3] * q4[k] - (k < 10 ? W.sgn[2] * q3[k] : 0.0);
     b2 = mr2_beta_k2(p2);
     b3 = mr2_beta_k3(p3);
     b4 = mr2_beta_k5(p4);
   }
-  /* beta_1 from the four three-cell linear fits, eqs. (2D-q1-1234)-(2D-beta1) */
+  /* beta_1 from the four three-cell linear fits, eqs. (2D-q1-1234)-(2D-beta1).
+     The six differences of the indicators xl2 + yt2, xr2 + yt2, xr2 + yb2,
+     xl2 + yb2 are, twice each, |dx| and |dy| with dx = xl2 - xr2,
+     dy = yt2 - yb2, and |dx + dy| + |dx - dy| = 2 max(|dx|, |dy|). */
   const double u5 = u[4];
   const double gxl = u5 - u[3], gxr = u[5] - u5, gyb = u5 - u[1], gyt = u[7] - u5;
-  const double xl2 = gxl * gxl, xr2 = gxr * gxr, yb2 = gyb * gyb, yt2 = gyt * gyt;
-  const double e11 = xl2 + yt2, e12 = xr2 + yt2, e13 = xr2 + yb2, e14 = xl2 + yb2;
-  double tau1 = (fabs(e11 - e12) + fabs(e11 - e13) + fabs(e11 - e14) + fabs(e12 - e13) +
-                 fabs(e12 - e14) + fabs(e13 - e14)) * (1.0 / 6.0);
+  const double xl2 = gxl * gxl, xr2 = gxr * gxr;
+  const double xle = xl2 + W.eps, xre = xr2 + W.eps;
+  const double yb2 = gyb * gyb, yt2 = gyt * gyt;
+  const double ddx = fabs(xl2 - xr2), ddy = fabs(yt2 - yb2);
+  double tau1 = (ddx + ddy + (ddx > ddy ? ddx : ddy)) * (1.0 / 3.0);
   tau1 = tau1 * tau1;
   /* normalised 1/4 (1 + tau1 / d_k) with one division (see the 1D case) */
-  const double f1 = e11 + W.eps, f2 = e12 + W.eps, f3 = e13 + W.eps, f4 = e14 + W.eps;
+  const double f1 = xle + yt2, f2 = xre + yt2, f3 = xre + yb2, f4 = xle + yb2;
   const double r12 = f1 * f2, r34 = f3 * f4;
   const double a11 = (f1 + tau1) * (f2 * r34);
   const double a12 = (f2 + tau1) * (f1 * r34);
   const double a13 = (f3 + tau1) * (r12 * f4);
   const double a14 = (f4 + tau1) * (r12 * f3);
-  const double ra = mr_rcp(a11 + a12 + a13 + a14);
-  const double gx = ((a11 + a14) * gxl + (a12 + a13) * gxr) * ra;
+  const double al = a11 + a14, ar = a12 + a13;
+  const double ra = mr_rcp(al + ar);
+  const double gx = (al * gxl + ar * gxr) * ra;
   const double gy = ((a11 + a12) * gyt + (a13 + a14) * gyb) * ra;
   const double b1 = gx * gx + gy * gy;
   double tau4 = (fabs(b4 - b1) + fabs(b4 - b2) + fabs(b4 - b3)) * (1.0 / 3.0);
@@ -229,16 +234,21 @@ MR_HD void mr_recon2d(const double u[9], const double v[9], const double w[9],
   const double o2 = W.g4[1] * (d2 + tau4) * (d1 * p34);
   const double o3 = W.g4[2] * (d3 + tau4) * (p12 * d4);
   const double o4 = W.g4[3] * (d4 + tau4) * (p12 * d3);
-  const double rs = mr_rcp(o1 + o2 + o3 + o4);
-  const double w1 = o1 * rs, w2 = o2 * rs, w3 = o3 * rs, w4 = o4 * rs;
-  const double c1 = w1 - w2 * W.sgn[0];
+  /* weights of q_1 .. q_4 (eq. re-p in terms of the q_l), halved: the
+     coefficients hold twice the polynomial (mr2_eval) */
+  const double rs = 0.5 * mr_rcp(o1 + o2 + o3 + o4);
+  const double w2 = o2 * rs, w3 = o3 * rs, w4 = o4 * rs;
+  const double c1 = o1 * rs - w2 * W.sgn[0];
   const double c2 = w2 * W.sg[1] - w3 * W.sgn[1];
   const double c3 = w3 * W.sg[2] - w4 * W.sgn[2];
   const double c4 = w4 * W.sg[3];
+  const double c23 = c2 + c3;   /* q_2 and q_3 share entries 0, 3, 4, 5 */
   double C[21];
-  C[0] = c1 * u5 + c2 * q2[0] + c3 * q3[0] + c4 * q4[0];
+  C[0] = c1 * (u5 + u5) + c23 * q3[0] + c4 * q4[0];
+  C[1] = c2 * q2[1] + c3 * q3[1] + c4 * q4[1];
+  C[2] = c2 * q2[2] + c3 * q3[2] + c4 * q4[2];
 #pragma unroll
-  for (int k = 1; k < 6; ++k) C[k] = c2 * q2[k] + c3 * q3[k] + c4 * q4[k];
+  for (int k = 3; k < 6; ++k) C[k] = c23 * q3[k] + c4 * q4[k];
 #pragma unroll
   for (int k = 6; k < 10; ++k) C[k] = c3 * q3[k] + c4 * q4[k];
 #pragma unroll
@@ -274,9 +284,10 @@ MR_HD void mr_euler_flux(const double* u, double gam, double* f) {
  * given r = 1/rho */
 MR_HD void mr_euler_fg_r(const double* u, double r, double gam, double* f, double* g) {
   const double vx = u[1] * r, vy = u[2] * r;
-  const double p = (gam - 1.0) * (u[3] - 0.5 * (u[1] * u[1] + u[2] * u[2]) * r);
-  f[0] = u[1]; f[1] = u[1] * vx + p; f[2] = u[2] * vx; f[3] = vx * (u[3] + p);
-  g[0] = u[2]; g[1] = u[1] * vy; g[2] = u[2] * vy + p; g[3] = vy * (u[3] + p);
+  const double fx = u[1] * vx, gy = u[2] * vy;
+  const double p = (gam - 1.0) * (u[3] - 0.5 * (fx + gy)), h = u[3] + p;
+  f[0] = u[1]; f[1] = fx + p; f[2] = u[2] * vx; f[3] = vx * h;
+  g[0] = u[2]; g[1] = f[2]; g[2] = gy + p; g[3] = vy * h;
 }
 
 MR_HD void mr_euler_fg(const double* u, double gam, double* f, double* g) {
@@ -315,10 +326,35 @@ MR_HD double mr_sqrtp(double x) {
 #endif
 }
 
+/* mr_sqrtp without the second correction, which only settles the rounding of
+ * the last bit: the first one already squares the error of the Goldschmidt
+ * step (below 2^-45). */
+MR_HD double mr_sqrt1(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const double r = __builtin_amdgcn_rsq(x);
+  double g = x * r, h = 0.5 * r;
+  const double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  return fma(fma(-g, g, x), h, g);
+#else
+  return sqrt(x);
+#endif
+}
+
 /* HLLC flux of eqs. (f_HLLC), (COEF), (uLR_) with the printed PVRS star
  * estimates; in 2D the normal direction D plays the role of mu and the
  * tangential momentum is carried in the star state.  Branches in the order
- * 0 <= sL, 0 <= s*, 0 <= sR, else. */
+ * 0 <= sL, 0 <= s*, 0 <= sR, else.
+ *
+ * The flux uses one side K: left for 0 <= sL or 0 <= s*, else right.  Only
+ * K's wave speed is formed: s_K - mu_K = -+ c_K coef_K with c_K coef_K =
+ * sqrt(gamma/rho_K (p_K + (gamma+1)/(2 gamma) max(p* - p_K, 0))), which needs
+ * neither p_K's reciprocal nor the other side's square root.  With s* < 0 the
+ * left speed matters only for mu_L >= c_L (coef >= 1), i.e. a supersonic
+ * left state: those lanes alone form sL first.  The kernels that call this
+ * are bound by FP64 issue: this form takes 102 FP64 instructions where both
+ * sides' speeds took 134. */
 template <int NC, int D>
 MR_HD void mr_hllc(const double* uL, const double* uR, double gam, double* f) {
   constexpr int N = 1 + D;
@@ -330,56 +366,48 @@ MR_HD void mr_hllc(const double* uL, const double* uR, double gam, double* f) {
   const double muL = uL[N] * irL, muR = uR[N] * irR;
   double m2L = uL[1] * uL[1], m2R = uR[1] * uR[1];
   if (NC == 4) { m2L += uL[2] * uL[2]; m2R += uR[2] * uR[2]; }
-  const double EL = uL[NC - 1], ER = uR[NC - 1];
-  const double pL = (gam - 1.0) * (EL - 0.5 * m2L * irL);
-  const double pR = (gam - 1.0) * (ER - 0.5 * m2R * irR);
-  const double cL = mr_sqrtp(gam * pL * irL), cR = mr_sqrtp(gam * pR * irR);
-  const double rs = 0.5 * (rL + rR), cs = 0.5 * (cL + cR);
-  const double crs = cs * rs;
-  /* 1/crs, 1/p_L, 1/p_R from one division */
-  const double pLR = pL * pR;
-  const double i3 = mr_rcp(crs * pLR);
-  const double icrs = pLR * i3, ipL = crs * pR * i3, ipR = crs * pL * i3;
+  const double pL = (gam - 1.0) * (uL[NC - 1] - 0.5 * irL * m2L);
+  const double pR = (gam - 1.0) * (uR[NC - 1] - 0.5 * irR * m2R);
+  const double giL = gam * irL, giR = gam * irR;
+  const double cL = mr_sqrt1(giL * pL), cR = mr_sqrt1(giR * pR);
+  const double crs = 0.25 * (rL + rR) * (cL + cR);   /* mean density times mean sound speed */
   const double ps = 0.5 * (pL + pR + (muL - muR) * crs);
-  const double ss = 0.5 * (muL + muR + (pL - pR) * icrs);   /* s* of the printed PVRS */
+  const double ss = 0.5 * (muL + muR + (pL - pR) * mr_rcp(crs));   /* s* of the printed PVRS */
   const double k1 = (gam + 1.0) / (2.0 * gam);
-  const double coefL = (ps <= pL) ? 1.0 : mr_sqrtp(1.0 + k1 * (ps * ipL - 1.0));
-  const double coefR = (ps <= pR) ? 1.0 : mr_sqrtp(1.0 + k1 * (ps * ipR - 1.0));
-  const double sL = muL - cL * coefL, sR = muR + cR * coefR;
-  /* ordered branch chain: 0 <= sL -> f_L; 0 <= s* -> f*_L; 0 <= sR -> f*_R; f_R */
-  const int br = (0.0 <= sL) ? 0 : ((0.0 <= ss) ? 1 : ((0.0 <= sR) ? 2 : 3));
-  const bool left = br <= 1;
-  const double* uK = left ? uL : uR;
-  const double sK = left ? sL : sR;
-  const double muK = left ? muL : muR;
-  const double rK = left ? rL : rR;
-  const double irK = left ? irL : irR;
-  const double pK = left ? pL : pR;
-  const double EK = left ? EL : ER;
-  double fK[NC];
-  fK[0] = uK[N];
-  fK[1] = uK[1] * muK;
-  if (NC == 4) fK[2] = uK[2] * muK;
-  fK[N] += pK;
-  fK[NC - 1] = muK * (EK + pK);
-  if (br == 0 || br == 3) {
+  /* c_K coef_K; a NaN p* stays one */
+  auto speed = [&](double gi, double p) { return mr_sqrt1(gi * (p + k1 * (ps <= p ? 0.0 : ps - p))); };
+  bool left = 0.0 <= ss;
+  if (!left && muL >= cL) left = 0.0 <= muL - speed(giL, pL);
+  double k[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) f[c] = fK[c];
-    return;
-  }
-  const double dsK = sK - muK;
+  for (int c = 0; c < NC; ++c) k[c] = left ? uL[c] : uR[c];
+  const double muK = left ? muL : muR, pK = left ? pL : pR, irK = left ? irL : irR;
+  const double w = speed(gam * irK, pK);
+  const double sK = left ? muK - w : muK + w;
+  /* f_K itself: 0 <= sL on the left, sR < 0 on the right -- and where a
+     point value has no sound speed (its pressure is not positive): every
+     comparison is then false, f_R is taken, and the NaN speeds must not
+     reach it */
+  const bool phys = (0.0 <= sK) == left;
+  double fK[NC];
+  fK[0] = k[N];
+  fK[1] = k[1] * muK;
+  if (NC == 4) fK[2] = k[2] * muK;
+  fK[N] += pK;
+  fK[NC - 1] = muK * (k[NC - 1] + pK);
   /* rho_K (s_K - mu_K) / (s_K - s*) and p_K / (rho_K (s_K - mu_K)) share one
      reciprocal */
-  const double rd = rK * dsK, den = sK - ss;
-  const double inv = mr_rcp(den * rd);
+  const double s = phys ? 0.0 : sK, sm = phys ? 0.0 : ss;
+  const double rd = k[0] * (s - muK), den = s - sm;
+  const double inv = phys ? 0.0 : mr_rcp(den * rd);
   const double fac = rd * rd * inv;
   double us[NC];
   us[0] = fac;
-  us[N] = fac * ss;
-  if (NC == 4) us[T] = fac * (uK[T] * irK);
-  us[NC - 1] = fac * (EK * irK + (ss - muK) * (ss + pK * den * inv));
+  us[N] = fac * sm;
+  if (NC == 4) us[T] = fac * (k[T] * irK);
+  us[NC - 1] = fac * (k[NC - 1] * irK + (sm - muK) * (sm + pK * (den * inv)));
 #pragma unroll
-  for (int c = 0; c < NC; ++c) f[c] = fK[c] + sK * (us[c] - uK[c]);
+  for (int c = 0; c < NC; ++c) f[c] = fK[c] + s * (us[c] - k[c]);
 }
 
 /* Burgers' f(u) = u^2/2 with global Lax-Friedrichs. */
