@@ -12,47 +12,74 @@
  * averages and y moments of rows y-2..y+2 (five rows: the modification of
  * the stencil's upper and lower cells reads rows y +- 2), the x moments of
  * rows y-1..y+1 (three rows); each value is loaded from HBM once per work
- * group, with the boundary condition applied when it is loaded, and the
+ * group, with the boundary condition applied when it is stored, and the
  * rows needed next are fetched into registers while the current row is
  * computed.  Flags of rows y-1..y+1 sit in a three-row LDS ring.
  *
  * Stage 1 also writes the first moments of U^n after Step 2.2 (I.unm), which
  * the combination of stages 2 and 3 uses.
  *
- * With NC = 4 the four lanes of a cell each reconstruct one conserved
- * component, then each lane takes one row eta_r of the cell's 4x4
- * Gauss-Lobatto grid for the volume integrals, the left-face flux at eta_r
- * and the bottom-face flux at xi_r.  The top-face flux of a row is the
- * bottom-face flux of the next one, so the residual of row j is completed
- * while row j+1 is processed.  mode 0..2 = RK stage, 3 = write L(U).
+ * With NC = 4 a wave holds 16 cells, lane = 16 k + cell: the four lanes of a
+ * cell each reconstruct one conserved component, then each lane takes one
+ * row eta_r of the cell's 4x4 Gauss-Lobatto grid for the volume integrals,
+ * the left-face flux at eta_r and the bottom-face flux at xi_r.  The sums
+ * over the rows and points, with their quadrature weights, are 4x4x4 FP64
+ * matrix products (mr2_sum): the contraction index of that instruction is
+ * lane / 16, so the lanes' values are its operand as they stand.  The
+ * top-face flux of a row is the bottom-face flux of the next one, so the
+ * residual of row j is completed while row j+1 is processed; the row's top
+ * trace waits in registers.  mode 0..2 = RK stage, 3 = write L(U).
  *
  * CH (characteristic-wise Step 1, NC = 4): lane k reconstructs field k of
  * the x set into the value slots, maps row eta_k of the cell back to the
  * conserved variables (R), takes the x-flux volume integral of that row
  * and the left-face flux; then the same with the y set for the y-flux
- * volume integral and the bottom-face flux, whose top traces the ring
- * keeps.  The moment rows of the next step are stored once both sets have
- * read the stencil. */
+ * volume integral and the bottom-face flux.  The moment rows of the next
+ * step are stored once both sets have read the stencil.
+ *
+ * What bounds it: FP64 issue.  A wave takes about 1,040 vector instructions
+ * a row step (860 of them FP64; 1,280 and 890 before the sums moved to
+ * matrix products, the top trace to registers and the ghost rules out of
+ * the staging of strips without ghosts), two waves a SIMD at 236 VGPRs and
+ * 76 KB of LDS a work group.  2048 x 2048, 56-row strips on 512 work
+ * groups: 922 -> 775 us a launch (33 TFLOP/s of the 71.8 an FP64 matrix
+ * product reaches); 800 x 200 with inflow sides, 8-row strips: 109 -> 101;
+ * 600 x 200 characteristic-wise: 254 -> 238.  Strips of 128 or 64 threads
+ * (30 or 14 owned columns) took 1.3 times as long: their narrower ring
+ * costs more than the shorter barriers give. */
 template <int NC>
 struct mr2_lds {
   static constexpr int CW = MR_BLOCK / NC;   /* strip cells incl. ring */
   static constexpr int XW = CW + 4;          /* staged columns */
   static constexpr int NP = 3 * NC;          /* staged planes per row step */
-  /* point-major layouts with padded strides: the lanes of one access
-     (cells cs, roles/components k) fall on distinct LDS banks */
-  static constexpr int CS = CW + 4;          /* component stride */
-  static constexpr int VS = NC * CS + 1;     /* point stride of val */
-  static constexpr int TS = NC * CS + 4;     /* point stride of top */
-  static constexpr int FS = NC * CS;         /* stride of fs */
-  /* plane strides chosen by measured LDS bank conflicts (mA padded by 2) */
-  static constexpr int XP = XW + 2;
+  /* strides (in doubles) that put the two groups of 16 cells a half wave
+     accesses 16 doubles apart modulo the 32 the banks hold; val reaches the
+     same with an exchange of 16-cell groups in the odd components */
+  static constexpr int CS = CW;              /* component stride of val */
+  static constexpr int VS = NC * CS + 4;     /* point stride of val */
+  static constexpr int FC = CW + 16;         /* component stride of fs */
+  static constexpr int FS = NC * FC + 16;    /* quantity stride of fs */
+  static constexpr int XP = NC == 1 ? XW : CW + 8;    /* plane stride of mA */
+  static constexpr int XB = NC == 1 ? XW : CW + 16;   /* plane stride of mB */
   double mA[5][2 * NC][XP];   /* planes (c, m = 0) and (c, m = 2): index 2c, 2c+1 */
-  double mB[3][NC][XW];       /* planes (c, m = 1)                               */
+  double mB[3][NC][XB];       /* planes (c, m = 1)                               */
   unsigned char flg[3][XW];
   double val[16 * VS];
-  double top[4 * TS];
-  double fs[2 * FS];
+  double fs[4 * FS];          /* left-face sums (weights w, w eta), bottom-face sums */
 };
+
+/* A operand of mr2_sum that puts weight w of the lane's row into output row i */
+MR_INL double mr2_wrow(int i, double w) { return (int)(threadIdx.x & 3) == i ? w : 0.0; }
+/* acc + the sum over the four lanes of a cell of b times the A operand's
+   weights: lane 16 i + cell receives output row i (a zero weight still
+   spreads a NaN over the cell's rows, never to another cell) */
+MR_INL double mr2_sum(double a, double b, double acc) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, acc, 0, 0, 0);
+#else
+  return acc + a * b;
+#endif
+}
 
 MR_INL int mr_mod3(int y) { return ((y % 3) + 3) % 3; }
 MR_INL int mr_mod5(int y) { return ((y % 5) + 5) % 5; }
@@ -66,15 +93,26 @@ MR_INL double mr2_stage_ld(const mr_grid& g, int e, int xs0, int y) {
   return mr_ld<STEP>(g, pl - 2 * NC, 1, xs0 + col, y);
 }
 
+/* the eigenvectors of direction D at the cell of staged column c0 whose row
+   sits in slot r; taken afresh where they are needed again (holding them
+   through Step 1 spills) */
+template <int D>
+MR_INL mr_char2 mr2_stage_char(const mr2_lds<4>& sh, int r, int c0, double gam) {
+  double u0[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) u0[c] = sh.mA[r][2 * c][c0];
+  return mr_char2_state<D>(u0, gam);
+}
+
 /* Characteristic-wise Step 1 (see mr_char2): field k of direction D of the
    cell at staged column c0, projected from the stencil in the LDS rings
    (the troubled cells' first moments modified when the cell is troubled)
    and reconstructed. */
 template <bool BP, int D>
 MR_INL void mr2_stage_field(const mr2_lds<4>& sh, const int* ra, const int* rb, const int* fs, int c0, int k,
-                            const mr_char2& e, const mr_wconst& W, double val[16]) {
+                            double gam, const mr_wconst& W, double val[16]) {
   double lk[4];
-  mr_char2_left<D>(e, k, lk);
+  mr_char2_left<D>(mr2_stage_char<D>(sh, ra[2], c0, gam), k, lk);
   double u[9], v[9], w[9];
 #pragma unroll
   for (int dy = 0; dy < 3; ++dy)
@@ -115,15 +153,28 @@ template <int NC, bool BP, int GB, bool CH>
 __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __restrict__ insts, const mr_tile2* __restrict__ tiles, int ntiles, int mode) {
   mr_kt_fill();
   using S = mr2_lds<NC>;
-  constexpr int CW = S::CW, XW = S::XW, NP = S::NP, CS = S::CS, VS = S::VS, TS = S::TS, FS = S::FS;
-  constexpr int NE = (NP * XW + MR_BLOCK - 1) / MR_BLOCK;   /* staged values per thread per row */
+  constexpr int CW = S::CW, XW = S::XW, NP = S::NP, CS = S::CS, VS = S::VS, FC = S::FC, FS = S::FS;
   __shared__ S sh;
   const int tid = threadIdx.x;
-  const int cs = tid / NC, k = tid % NC;
-  const int comp = (NC == 1) ? 0 : k;
-#define VAL(p, c, cell) sh.val[(p) * VS + (c) * CS + (cell)]
-#define TOP(q, c, cell) sh.top[(q) * TS + (c) * CS + (cell)]
-#define FSM(m, c, cell) sh.fs[(m) * FS + (c) * CS + (cell)]
+  const int k = (NC == 1) ? 0 : (tid >> 4) & 3;
+  const int cs = (NC == 1) ? tid : 16 * (tid >> 6) + (tid & 15);
+  const int comp = k;
+#define VAL(p, c, cell) sh.val[(p) * VS + (c) * CS + ((cell) ^ (NC == 1 ? 0 : ((c) & 1) << 4))]
+#define FSM(m, c, cell) sh.fs[(m) * FS + (c) * FC + (cell)]
+  /* staging: thread (component gc, column tid % CW) loads its column's three
+     moments in every row step; the four columns beyond CW are the first 12
+     threads' of each component (moment em, column ecol).  The moments are
+     staged at different rows (x moments one row behind) */
+  const int gc = NC == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / CW);
+  const int gcol = tid % CW, em = gcol >> 2, ecol = CW + (gcol & 3);
+  const bool ext = gcol < 12;
+  /* quadrature weights of this lane's row as A operands (see mr2_sum) */
+  const double lw = glw(k), lwe = glw(k) * gln(k);
+  double aF[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) aF[c] = mr2_wrow(c, lw * MR_W0);
+  const double aX = (tid & 1) ? mr2_wrow(1, lwe) : mr2_wrow(0, lw);
+  const double aY = (tid & 1) ? mr2_wrow(3, lwe) : mr2_wrow(2, lw);
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const mr_tile2 tl = tiles[t];
     const mr_inst& I = insts[tl.inst];
@@ -137,30 +188,26 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
     const double alpha = (NC == 1) ? mr_bitsd(I.lfa[st]) : 0.0;
     MR_GLB double* O = mr_gp(I.p_out[st]);
     const long long P = I.plane;
+    const int nx = I.nx;
     const int xs0 = tl.x0 - 3;                 /* strip column 0 */
     const int x = tl.x0 - 1 + cs;
     const bool outx = cs >= 1 && cs <= CW - 2 && x < I.nx;
-    /* staged element q of this thread in every row step: plane and folded
-       column as one element offset (A planes: bit 30 set); whether it is a
-       first moment of a transmissive x ghost (reads as zero) or flips sign
-       as a reflective x ghost; whether it is a first moment, and whether it
-       flips in a reflective y ghost row */
-    int soff[NE];
-    unsigned szero = 0u, sfm = 0u, sneg = 0u, syflip = 0u;
-#pragma unroll
-    for (int q = 0; q < NE; ++q) {
-      const int e = min(tid + q * MR_BLOCK, NP * XW - 1);
-      const int pl = e / XW, col = e % XW;
-      const bool isA = pl < 2 * NC;
-      const int c = isA ? pl / 2 : pl - 2 * NC, m = isA ? (pl % 2) * 2 : 1;
-      int kx = 0;
-      const int ii = mr_fold(xs0 + col, I.nx, I.bcx, &kx);
-      soff[q] = ((c * 3 + m) * (int)P + ii) | (isA ? (1 << 30) : 0);
-      if (m != 0) sfm |= 1u << q;
-      if (m != 0 && kx == 1) szero |= 1u << q;
-      if (kx == 2 && mr_refl_flip(c, m, 0)) sneg |= 1u << q;
-      if (mr_refl_flip(c, m, 1)) syflip |= 1u << q;
-    }
+    /* folded columns of this thread's staged elements and their x ghost
+       kinds; xplain: no staged column of the strip is a ghost that changes
+       its value (uniform) */
+    int kx = 0, kxe = 0;
+    const int ii = mr_fold(xs0 + gcol, nx, I.bcx, &kx);
+    const int iie = mr_fold(xs0 + ecol, nx, I.bcx, &kxe);
+    const bool xplain = (xs0 >= 0 || (I.bcx & 3) == 0) && (xs0 + XW <= nx || ((I.bcx >> 2) & 3) == 0);
+    const MR_GLB double* ub = g.U + (long long)(3 * gc) * P;      /* component gc */
+    const MR_GLB double* ue = ub + (ext ? (long long)em * P + iie : 0);
+    /* value of a staged element of moment m: zero as a first moment of a
+       transmissive ghost, the sign of a reflective one */
+    auto ghost = [&](double v, int m, int kxx, int ky) {
+      const bool neg = (kxx == 2 && mr_refl_flip(gc, m, 0)) != (ky == 2 && mr_refl_flip(gc, m, 1));
+      return (m != 0 && (kxx == 1 || ky == 1)) ? 0.0 : (neg ? -v : v);
+    };
+    auto flag_ld = [&](int e, int row) { return (unsigned char)mr_flag(fl, I.fex, I.fey, I.fhalo, xs0 + e, row); };
     /* ---- prologue: A rows y0-3 .. y0+1, B and flag rows y0-2 .. y0 ---- */
     for (int r = tl.y0 - 3; r <= tl.y0 - 2; ++r)
       for (int e = tid; e < 2 * NC * XW; e += MR_BLOCK)
@@ -171,73 +218,59 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
         if (e / XW < 2 * NC) sh.mA[mr_mod5(r + 1)][e / XW][e % XW] = v;
         else sh.mB[mr_mod3(r)][e / XW - 2 * NC][e % XW] = v;
       }
-      for (int e = tid; e < XW; e += MR_BLOCK)
-        sh.flg[mr_mod3(r)][e] = (unsigned char)mr_flag(fl, I.fex, I.fey, I.fhalo, xs0 + e, r);
+      for (int e = tid; e < XW; e += MR_BLOCK) sh.flg[mr_mod3(r)][e] = flag_ld(e, r);
     }
     __syncthreads();
-    double pAu = 0.0, pAv = 0.0, pAw = 0.0, pB0 = 0.0, pB1 = 0.0, pU = 0.0, pV = 0.0, pW = 0.0;
+    double pAu = 0.0, pAv = 0.0, pAw = 0.0, pU = 0.0, pV = 0.0, pW = 0.0;
+    double tp[4 / NC][NC];   /* top trace of the row below at this lane's points */
+#pragma unroll
+    for (int rr = 0; rr < 4 / NC; ++rr)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) tp[rr][c] = 0.0;
     for (int jr = -1; jr <= tl.rows; ++jr) {
       const int y = tl.y0 + jr;
       /* stages 2 and 3: U^n of the row finished in this step, loaded now so
          that the latency hides behind the reconstruction */
       double qun = 0.0, qvn = 0.0, qwn = 0.0;
       if ((mode == 1 || mode == 2) && jr >= 1 && outx) {
-        const long long cell = (long long)(y - 1) * I.nx + x;
+        const long long cell = (long long)(y - 1) * nx + x;
         const MR_GLB double* vs = I.mod == 0 ? unm + (long long)(comp * 2) * P : gn.U + (long long)(comp * 3 + 1) * P;
         qun = gn.U[(long long)(comp * 3) * P + cell];
         qvn = vs[cell];
         qwn = vs[P + cell];
       }
       /* prefetch A row y+3, B and flag row y+2 (stored once rows y-2 and
-         y-1 are consumed) */
-      double pre[NE];
-      unsigned pzero = 0u, pneg = 0u;   /* elements that read as zero / flip (applied when stored) */
-      unsigned char pref = 0;
-      {
-        /* row folds are uniform over the work group */
-        int kA = 0, kB = 0;
-        const int jA = mr_fold(y + 3, I.ny, I.bcy, &kA) * I.nx;
-        const int jB = mr_fold(y + 2, I.ny, I.bcy, &kB) * I.nx;
-#pragma unroll
-        for (int q = 0; q < NE; ++q) {
-          const int o = soff[q];
-          const bool isA = (o >> 30) & 1;
-          const int off = (o & ((1 << 30) - 1)) + (isA ? jA : jB);
-          pre[q] = g.U[off];
-          const int ky = isA ? kA : kB;
-          /* first moments of transmissive ghosts are zero; reflective ghosts
-             flip the moments mr_refl_flip names */
-          if (((szero >> q) & 1u) || (((sfm >> q) & 1u) && ky == 1)) pzero |= 1u << q;
-          if (((sneg >> q) & 1u) != (ky == 2 && ((syflip >> q) & 1u))) pneg |= 1u << q;
-        }
-      }
-      if (tid < XW) pref = (unsigned char)mr_flag(fl, I.fex, I.fey, I.fhalo, xs0 + tid, y + 2);
+         y-1 are consumed); the row folds are uniform over the work group */
+      int kA = 0, kB = 0;
+      const long long jA = (long long)mr_fold(y + 3, I.ny, I.bcy, &kA) * nx;
+      const long long jB = (long long)mr_fold(y + 2, I.ny, I.bcy, &kB) * nx;
+      const double pre0 = (ub + jA)[ii], pre1 = (ub + P + jB)[ii], pre2 = (ub + 2 * P + jA)[ii];
+      double pree = 0.0;
+      if (ext) pree = ue[em == 1 ? jB : jA];
+      unsigned char pref = 0, prefe = 0;
+      if (tid < XW) pref = flag_ld(tid, y + 2);
+      if (XW > MR_BLOCK && tid < XW - MR_BLOCK) prefe = flag_ld(MR_BLOCK + tid, y + 2);
       /* ---- Steps 1, 2.2, 2.3 for component `comp` of cell (x, y) ---- */
-      double cu, cv, cw;
+      double cu = 0.0, cv = 0.0, cw = 0.0;
       /* characteristic-wise: the stencil rows, flags and the cell's state */
       int cra[5], crb[3], cfs[9];
-      mr_char2 ex{}, ey{};
       if constexpr (CH) {
         const int c0 = cs + 2;
         for (int q = 0; q < 5; ++q) cra[q] = mr_mod5(y - 2 + q);
         for (int q = 0; q < 3; ++q) crb[q] = mr_mod3(y - 1 + q);
 #pragma unroll
         for (int l = 0; l < 9; ++l) cfs[l] = sh.flg[crb[l / 3]][c0 + l % 3 - 1];
-        double u0[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) u0[c] = sh.mA[cra[2]][2 * c][c0];
-        ex = mr_char2_state<0>(u0, gam);
-        ey = mr_char2_state<1>(u0, gam);
-        cu = u0[comp];
-        const bool md = cfs[4] && I.mod != 1;
-        cv = md ? mr_modified_moment(sh.mA[cra[2]][2 * comp][c0 - 1], sh.mA[cra[2]][2 * comp][c0 + 1],
-                                     sh.mB[crb[1]][comp][c0 - 1], sh.mB[crb[1]][comp][c0 + 1])
-                : sh.mB[crb[1]][comp][c0];
-        cw = md ? mr_modified_moment(sh.mA[cra[1]][2 * comp][c0], sh.mA[cra[3]][2 * comp][c0],
-                                     sh.mA[cra[1]][2 * comp + 1][c0], sh.mA[cra[3]][2 * comp + 1][c0])
-                : sh.mA[cra[2]][2 * comp + 1][c0];
+          /* the cell's own moments for the combination */
+          const bool md = cfs[4] && I.mod != 1;
+          cu = sh.mA[cra[2]][2 * comp][c0];
+          cv = md ? mr_modified_moment(sh.mA[cra[2]][2 * comp][c0 - 1], sh.mA[cra[2]][2 * comp][c0 + 1],
+                                       sh.mB[crb[1]][comp][c0 - 1], sh.mB[crb[1]][comp][c0 + 1])
+                  : sh.mB[crb[1]][comp][c0];
+          cw = md ? mr_modified_moment(sh.mA[cra[1]][2 * comp][c0], sh.mA[cra[3]][2 * comp][c0],
+                                       sh.mA[cra[1]][2 * comp + 1][c0], sh.mA[cra[3]][2 * comp + 1][c0])
+                  : sh.mA[cra[2]][2 * comp + 1][c0];
         double val[16];
-        mr2_stage_field<BP, 0>(sh, cra, crb, cfs, c0, comp, ex, I.W, val);
+        mr2_stage_field<BP, 0>(sh, cra, crb, cfs, c0, comp, gam, I.W, val);
 #pragma unroll
         for (int q = 0; q < 16; ++q) VAL(q, comp, cs) = val[q];
       } else {
@@ -254,8 +287,8 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
             u[l] = sh.mA[ra[dy + 1]][2 * comp][c0 + dx - 1];
             v[l] = sh.mB[rb[dy]][comp][c0 + dx - 1];
             w[l] = sh.mA[ra[dy + 1]][2 * comp + 1][c0 + dx - 1];
-            fs[l] = sh.flg[rb[dy]][c0 + dx - 1];
           }
+        fs[4] = sh.flg[rb[1]][c0];
         if (fs[4]) {
           /* troubled cell: first moments of the troubled cells of the
              stencil modified from the unmodified input (Jacobi) */
@@ -264,6 +297,7 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
 #pragma unroll
             for (int dx = 0; dx < 3; ++dx) {
               const int l = dx + 3 * dy;
+              fs[l] = sh.flg[rb[dy]][c0 + dx - 1];
               if (!fs[l]) continue;
               const int cc = c0 + dx - 1;
               v[l] = mr_modified_moment(sh.mA[ra[dy + 1]][2 * comp][cc - 1], sh.mA[ra[dy + 1]][2 * comp][cc + 1],
@@ -287,52 +321,56 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
          A row y+3 and B/flag row y+2 */
       auto store_rows = [&]() {
         const int sa = mr_mod5(y + 3), sb = mr_mod3(y + 2);
-#pragma unroll
-        for (int q = 0; q < NE; ++q) {
-          const int e = tid + q * MR_BLOCK;
-          if (e < NP * XW) {
-            const double v = ((pzero >> q) & 1u) ? 0.0 : (((pneg >> q) & 1u) ? -pre[q] : pre[q]);
-            if (e / XW < 2 * NC) sh.mA[sa][e / XW][e % XW] = v;
-            else sh.mB[sb][e / XW - 2 * NC][e % XW] = v;
-          }
+        if (xplain && kA == 0 && kB == 0) {
+          sh.mA[sa][2 * gc][gcol] = pre0;
+          sh.mB[sb][gc][gcol] = pre1;
+          sh.mA[sa][2 * gc + 1][gcol] = pre2;
+          if (ext) (em == 1 ? sh.mB[sb][gc] : sh.mA[sa][2 * gc + (em >> 1)])[ecol] = pree;
+        } else {
+          sh.mA[sa][2 * gc][gcol] = ghost(pre0, 0, kx, kA);
+          sh.mB[sb][gc][gcol] = ghost(pre1, 1, kx, kB);
+          sh.mA[sa][2 * gc + 1][gcol] = ghost(pre2, 2, kx, kA);
+          if (ext)
+            (em == 1 ? sh.mB[sb][gc] : sh.mA[sa][2 * gc + (em >> 1)])[ecol] = ghost(pree, em, kxe, em == 1 ? kB : kA);
         }
         if (tid < XW) sh.flg[sb][tid] = pref;
+        if (XW > MR_BLOCK && tid < XW - MR_BLOCK) sh.flg[sb][MR_BLOCK + tid] = prefe;
         if (GB && mr_presc_rows<GB == 2>(I, xs0, XW, y + 2, 2)) {
-          /* ghosts that hold prescribed data */
+          /* ghosts that hold prescribed data, by the threads that stored them */
           const double tb = mr_stage_time(I, mode);
 #pragma unroll 1
-          for (int q = 0; q < NE; ++q) {
-            const int e = tid + q * MR_BLOCK;
-            if (e < NP * XW) {
-              const int pl = e / XW, col = e % XW;
-              const bool isA = pl < 2 * NC;
-              const int c = isA ? pl / 2 : pl - 2 * NC, m = isA ? (pl % 2) * 2 : 1;
-              double v;
-              if (mr_presc(I, c, m, xs0 + col, isA ? y + 3 : y + 2, tb, &v) ||
-                  (GB == 2 && mr_step_val(I, g.U, c, m, xs0 + col, isA ? y + 3 : y + 2, &v))) {
-                if (isA) sh.mA[sa][pl][col] = v;
-                else sh.mB[sb][pl - 2 * NC][col] = v;
-              }
+          for (int q = 0; q < 4; ++q) {
+            if (q == 3 && !ext) continue;
+            const int m = q < 3 ? q : em, col = q < 3 ? gcol : ecol, row = m == 1 ? y + 2 : y + 3;
+            double v;
+            if (mr_presc(I, gc, m, xs0 + col, row, tb, &v) ||
+                (GB == 2 && mr_step_val(I, g.U, gc, m, xs0 + col, row, &v))) {
+              if (m == 1) sh.mB[sb][gc][col] = v;
+              else sh.mA[sa][2 * gc + (m >> 1)][col] = v;
             }
           }
         }
       };
       /* ---- volume integrals and the fluxes this lane owns ---- */
-      double F[NC], G[NC], XL0[NC], XL1[NC], YB0[NC], YB1[NC];
+      /* F, G: twelve times the xi quadrature of the row; fx, gy: the fluxes */
+      double F[4 / NC][NC], G[4 / NC][NC], fx[4 / NC][NC], gy[4 / NC][NC];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) F[c] = G[c] = XL0[c] = XL1[c] = YB0[c] = YB1[c] = 0.0;
+      for (int rr = 0; rr < 4 / NC; ++rr)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) F[rr][c] = G[rr][c] = fx[rr][c] = gy[rr][c] = 0.0;
+      double fF = 0.0, fG = 0.0, fs4[4] = {0.0, 0.0, 0.0, 0.0};
       const bool body = jr >= 0 && jr < tl.rows;
       if constexpr (CH) {
         /* lane k = row eta_k of the cell: x set back to conserved variables */
         const int r = k;
-        const double wr = glw(r), er = gln(r);
-        double pts[4][4];
+        double pts[4][4], fq[4][4];
+        mr_char2 ec = mr2_stage_char<0>(sh, cra[2], cs + 2, gam);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           double wq[4];
 #pragma unroll
           for (int j = 0; j < 4; ++j) wq[j] = VAL(q + 4 * r, j, cs);
-          mr_char2_right<0>(ex, wq, pts[q]);
+          mr_char2_right<0>(ec, wq, pts[q]);
         }
         /* row eta_k of the cell is read and written by lane k only */
 #pragma unroll
@@ -341,39 +379,42 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
           for (int c = 0; c < 4; ++c) VAL(q + 4 * r, c, cs) = pts[q][c];
         if (body) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            double f[4];
-            mr_euler_flux<4, 0>(pts[q], gam, f);
-            const double wq = glw(q) * wr;
+          for (int q = 0; q < 4; ++q) mr_euler_flux<4, 0>(pts[q], gam, fq[q]);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) F[c] += wq * f[c];
-          }
+          for (int c = 0; c < 4; ++c) F[0][c] = (fq[0][c] + fq[3][c]) + 5.0 * (fq[1][c] + fq[2][c]);
         }
         __syncthreads();
         if (body && cs >= 1) {
-          double a[4], fh[4];
+          double a[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c) a[c] = VAL(3 + 4 * r, c, cs - 1);
-          mr_face_flux<4, 0, GB == 2>(I, a, pts[0], gam, alpha, x, y, mr_stage_time(I, mode), fh);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) { XL0[c] += wr * fh[c]; XL1[c] += wr * er * fh[c]; }
+          mr_face_flux<4, 0, GB == 2>(I, a, pts[0], gam, alpha, x, y, mr_stage_time(I, mode), fx[0]);
         }
         __syncthreads();
+        /* the x set's sums at once: four registers instead of sixteen held
+           through the y set's Step 1 */
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          fF = mr2_sum(aF[c], F[0][c], fF);
+          fs4[c] = mr2_sum(aX, fx[0][c], 0.0);
+        }
         /* field k of the y set (the stencil rows are still in place) */
         {
+          const int c0 = cs + 2;
           double val[16];
-          mr2_stage_field<BP, 1>(sh, cra, crb, cfs, cs + 2, comp, ey, I.W, val);
+          mr2_stage_field<BP, 1>(sh, cra, crb, cfs, c0, comp, gam, I.W, val);
 #pragma unroll
           for (int q = 0; q < 16; ++q) VAL(q, comp, cs) = val[q];
         }
         __syncthreads();
         store_rows();
+        ec = mr2_stage_char<1>(sh, cra[2], cs + 2, gam);   /* row y's slot is not the one stored */
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           double wq[4];
 #pragma unroll
           for (int j = 0; j < 4; ++j) wq[j] = VAL(q + 4 * r, j, cs);
-          mr_char2_right<1>(ey, wq, pts[q]);
+          mr_char2_right<1>(ec, wq, pts[q]);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -381,91 +422,98 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
           for (int c = 0; c < 4; ++c) VAL(q + 4 * r, c, cs) = pts[q][c];
         if (body) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            double g4[4];
-            mr_euler_flux<4, 1>(pts[q], gam, g4);
-            const double wq = glw(q) * wr;
+          for (int q = 0; q < 4; ++q) mr_euler_flux<4, 1>(pts[q], gam, fq[q]);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) G[c] += wq * g4[c];
-          }
+          for (int c = 0; c < 4; ++c) G[0][c] = (fq[0][c] + fq[3][c]) + 5.0 * (fq[1][c] + fq[2][c]);
         }
         __syncthreads();
         if (jr >= 0) {
-          double a[4], b[4], gh[4];
+          double b[4];
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            a[c] = TOP(r, c, cs);
-            b[c] = VAL(r, c, cs);
-          }
-          mr_face_flux<4, 1, GB == 2>(I, a, b, gam, alpha, y, x, mr_stage_time(I, mode), gh);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) { YB0[c] += wr * gh[c]; YB1[c] += wr * er * gh[c]; }
+          for (int c = 0; c < 4; ++c) b[c] = VAL(r, c, cs);
+          mr_face_flux<4, 1, GB == 2>(I, tp[0], b, gam, alpha, y, x, mr_stage_time(I, mode), gy[0]);
         }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) tp[0][c] = VAL(12 + r, c, cs);
       } else {
-      store_rows();
+        store_rows();
 #pragma unroll
-      for (int rr = 0; rr < 4 / NC; ++rr) {
-        const int r = (NC == 1) ? rr : k;
-        const double wr = glw(r), er = gln(r);
-        if (body) {
-          double pts[4][NC], rr4[4];
+        for (int rr = 0; rr < 4 / NC; ++rr) {
+          const int r = (NC == 1) ? rr : k;
+          if (body) {
+            double pts[4][NC], f[4][NC], gg[4][NC];
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) pts[q][c] = VAL(q + 4 * r, c, cs);
-          if (NC == 4) mr_recip4(pts[0][0], pts[1][0], pts[2][0], pts[3][0], rr4);
+              for (int c = 0; c < NC; ++c) pts[q][c] = VAL(q + 4 * r, c, cs);
+            if constexpr (NC == 4) {
+              double rr4[4];
+              mr_recip4(pts[0][0], pts[1][0], pts[2][0], pts[3][0], rr4);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            double f[NC], gg[NC];
-            if (NC == 4) mr_euler_fg_r(pts[q], rr4[q], gam, f, gg);
-            else { f[0] = 0.5 * pts[q][0] * pts[q][0]; gg[0] = f[0]; }
-            const double wq = glw(q) * wr;
+              for (int q = 0; q < 4; ++q) mr_euler_fg_r(pts[q], rr4[q], gam, f[q], gg[q]);
+            } else {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) { F[c] += wq * f[c]; G[c] += wq * gg[c]; }
-          }
-          if (cs >= 1) {
-            double a[NC], b[NC], fh[NC];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-              a[c] = VAL(3 + 4 * r, c, cs - 1);
-              b[c] = VAL(4 * r, c, cs);
+              for (int q = 0; q < 4; ++q) f[q][0] = gg[q][0] = 0.5 * pts[q][0] * pts[q][0];
             }
-            mr_face_flux<NC, 0, GB == 2>(I, a, b, gam, alpha, x, y, mr_stage_time(I, mode), fh);
 #pragma unroll
-            for (int c = 0; c < NC; ++c) { XL0[c] += wr * fh[c]; XL1[c] += wr * er * fh[c]; }
+            for (int c = 0; c < NC; ++c) F[rr][c] = (f[0][c] + f[3][c]) + 5.0 * (f[1][c] + f[2][c]);
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+              G[rr][c] = (NC == 4 && c == 1) ? F[rr][NC / 2] : (gg[0][c] + gg[3][c]) + 5.0 * (gg[1][c] + gg[2][c]);
+            if (cs >= 1) {
+              double a[NC];
+#pragma unroll
+              for (int c = 0; c < NC; ++c) a[c] = VAL(3 + 4 * r, c, cs - 1);
+              mr_face_flux<NC, 0, GB == 2>(I, a, pts[0], gam, alpha, x, y, mr_stage_time(I, mode), fx[rr]);
+            }
           }
-        }
-        if (jr >= 0) {
-          double a[NC], b[NC], gh[NC];
+          if (jr >= 0) {
+            double b[NC];
 #pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            a[c] = TOP(r, c, cs);
-            b[c] = VAL(r, c, cs);
+            for (int c = 0; c < NC; ++c) b[c] = VAL(r, c, cs);
+            mr_face_flux<NC, 1, GB == 2>(I, tp[rr], b, gam, alpha, y, x, mr_stage_time(I, mode), gy[rr]);
           }
-          mr_face_flux<NC, 1, GB == 2>(I, a, b, gam, alpha, y, x, mr_stage_time(I, mode), gh);
 #pragma unroll
-          for (int c = 0; c < NC; ++c) { YB0[c] += wr * gh[c]; YB1[c] += wr * er * gh[c]; }
+          for (int c = 0; c < NC; ++c) tp[rr][c] = VAL(12 + r, c, cs);
         }
       }
+      /* the quadratures over the rows: lane k receives component k's volume
+         sums; the face sums of all components go through LDS */
+      if constexpr (NC == 4) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (!CH) fF = mr2_sum(aF[c], F[0][c], fF);
+          fG = mr2_sum(aF[c], G[0][c], fG);
+          if (!CH) fs4[c] = mr2_sum(aX, fx[0][c], 0.0);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) FSM(k, c, cs) = mr2_sum(aY, gy[0][c], fs4[c]);
+      } else {
+        double q0 = 0.0, q1 = 0.0, q2 = 0.0, q3 = 0.0;
+#pragma unroll
+        for (int rr = 0; rr < 4 / NC; ++rr) {
+          const double wr = glw(rr), we = glw(rr) * gln(rr);
+          fF += wr * MR_W0 * F[rr][0]; fG += wr * MR_W0 * G[rr][0];
+          q0 += wr * fx[rr][0]; q1 += we * fx[rr][0];
+          q2 += wr * gy[rr][0]; q3 += we * gy[rr][0];
+        }
+        FSM(0, 0, cs) = q0; FSM(1, 0, cs) = q1; FSM(2, 0, cs) = q2; FSM(3, 0, cs) = q3;
       }
-      /* lane k collects component k's sums */
-      const double fF = mr_rs<NC>(F, k), fG = mr_rs<NC>(G, k);
-      const double xl0 = mr_rs<NC>(XL0, k), xl1 = mr_rs<NC>(XL1, k);
-      const double yb0 = mr_rs<NC>(YB0, k), yb1 = mr_rs<NC>(YB1, k);
-      FSM(0, comp, cs) = xl0;
-      FSM(1, comp, cs) = xl1;
+      /* (the next row's values are written after this barrier, its face sums
+         after the one that follows, so the row needs no third) */
       __syncthreads();
-      /* the row below has consumed its top trace; store this row's */
-#pragma unroll
-      for (int q = 0; q < 4; ++q) TOP(q, comp, cs) = VAL(12 + q, comp, cs);
+      const double xl0 = FSM(0, comp, cs), xl1 = FSM(1, comp, cs);
+      const double yb0 = FSM(2, comp, cs), yb1 = FSM(3, comp, cs);
+      const int cr = cs + 1 < CW ? cs + 1 : cs;
+      const double xr0 = FSM(0, comp, cr), xr1 = FSM(1, comp, cr);
       /* ---- finish the row below: its top face is this row's bottom face ---- */
       if (jr >= 1 && outx) {
         const int yp = y - 1;
-        const double Lu = pAu - (yb0 - pB0) * rdy;
-        const double Lv = pAv - (yb1 - pB1) * rdy;
-        const double Lw = pAw - (yb0 + pB0) * (0.5 * rdy);
+        const double Lu = pAu - yb0 * rdy;
+        const double Lv = pAv - yb1 * rdy;
+        const double Lw = pAw - yb0 * (0.5 * rdy);
         double r0, r1, r2;
-        const long long cell = (long long)yp * I.nx + x;
+        const long long cell = (long long)yp * nx + x;
         if (mode == 3) { r0 = Lu; r1 = Lv; r2 = Lw; }
         else if (mode == 0) {
           r0 = pU + dt * Lu; r1 = pV + dt * Lv; r2 = pW + dt * Lw;
@@ -488,23 +536,15 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
         O[(long long)(comp * 3 + 2) * P + cell] = r2;
       }
       /* ---- this row's partial residual (all but the top face) ---- */
-      if (cs + 1 < CW) {
-        const double xr0 = FSM(0, comp, cs + 1);
-        const double xr1 = FSM(1, comp, cs + 1);
-        pAu = -(xr0 - xl0) * rdx;
-        pAv = -(xr0 + xl0) * (0.5 * rdx) + fF * rdx;
-        pAw = -(xr1 - xl1) * rdx + fG * rdy;
-      }
-      pB0 = yb0;
-      pB1 = yb1;
+      pAu = -(xr0 - xl0) * rdx + yb0 * rdy;
+      pAv = (fF - 0.5 * (xr0 + xl0)) * rdx + yb1 * rdy;
+      pAw = (fG - 0.5 * yb0) * rdy - (xr1 - xl1) * rdx;
       pU = cu;
       pV = cv;
       pW = cw;
-      __syncthreads();
     }
   }
 #undef VAL
-#undef TOP
 #undef FSM
 }
 

@@ -1,5 +1,6 @@
-"""The 2D stage kernel on the rare branches of its HLLC flux, against the
-oracle: residual within 1e-12 of each component's
+"""The 2D stage kernel at the edges of its strips (a strip owns 62 Euler or
+254 Burgers columns and stages two more each side) and the branches of its
+HLLC flux, against the oracle: residual within 1e-12 of each component's
 scale over dt, flags bit for bit (the bars of the other parity tests)."""
 import numpy as np
 import pytest
@@ -25,6 +26,35 @@ def _residual(prob, U):
     assert d.max() <= TOL, d
     assert np.array_equal(fl.cpu().numpy(), flref)
     return flref
+
+
+def _euler(nx, ny, bc, seed=3):
+    """Random smooth-free Euler data (jumps everywhere): every cell's branch differs."""
+    rng = np.random.default_rng(seed)
+    prob = I.Problem(dim=2, nx=nx, ny=ny, x1=nx / ny, bc_x=bc, bc_y=bc)
+    r, p = rng.uniform(0.5, 1.5, (2, ny, nx))
+    u, v = rng.uniform(-0.5, 0.5, (2, ny, nx))
+    U = np.zeros(prob.shape())
+    U[:, 0] = I.euler2d_cons(r, u, v, p, 1.4)
+    U[:, 1:] = 0.02 * rng.uniform(-1, 1, (4, 2, ny, nx))
+    return prob, U
+
+
+@pytest.mark.parametrize("bc", [I.PERIODIC, I.TRANSMISSIVE, I.REFLECTIVE])
+@pytest.mark.parametrize("nx", [8, 61, 62, 63, 66, 124, 125])
+def test_strip_edges(nx, bc):
+    prob, U = _euler(nx, 9, bc)
+    assert _residual(prob, U).any()
+
+
+@pytest.mark.parametrize("nx", [253, 254, 255, 258, 509])
+def test_strip_edges_burgers(nx):
+    rng = np.random.default_rng(5)
+    prob = I.Problem(dim=2, nx=nx, ny=10, x1=nx / 10.0, system=I.BURGERS)
+    U = np.zeros(prob.shape())
+    U[0, 0] = rng.uniform(-1.0, 1.0, (10, nx))
+    U[0, 1:] = 0.05 * rng.uniform(-1, 1, (2, 10, nx))
+    assert _residual(prob, U)[:, 240:].any()
 
 
 @pytest.mark.parametrize("axis", [0, 1])
