@@ -273,7 +273,10 @@ mrhweno_status mrhweno_residual_noalloc(const mrhweno_problem* prob, const void*
                                         void* residual_dev, void* flags_dev, void* hip_stream);
 
 /* Rows per work item of the 2D stage kernel and grid size (0 = one work
- * group per work item) -- the launch shape the autotuner chooses. */
+ * group per work item) -- the launch shape the autotuner chooses.  Where
+ * work items of that height would leave the GPU short of work (fewer than
+ * 512 in a launch) the library takes lower ones; without this call it
+ * chooses the height itself.  Results do not depend on it. */
 mrhweno_status mrhweno_set_launch(mrhweno_ctx* ctx, int rows_2d, int grid_2d);
 
 /* Autotuner: time the 2D stage kernel (in its residual-only mode, which

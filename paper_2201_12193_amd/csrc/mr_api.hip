@@ -45,7 +45,9 @@ constexpr int kBlock = 256;
 constexpr int kFused1 = kBlock - 6;   /* cells of a tile of the step's 1D kernel (three ring cells each side) */
 constexpr int kFHalo = 2;   /* flags: final values of cells -1..n need flags -2..n+1 */
 constexpr int kSHalo = 3;   /* summaries: flags of cells -2..n+1 need summaries -3..n+2 */
-constexpr int kMinRows = 8; /* smallest 2D strip height the work lists are sized for */
+constexpr int kMinRows = 8; /* smallest 2D strip height a caller may set              */
+constexpr int kDefRows = 32; /* 2D strip height at most, unless a caller sets one       */
+constexpr int kFewStrips = 1024; /* strips of a launch whose strips are lower than kMinRows, at most */
 constexpr int kKxW = 62;    /* 2D KXRCF work item: 62 flag columns ...                */
 constexpr int kKxRows = 46; /* ... x up to 46 flag rows of the extended flag range    */
 constexpr int kKxMinRows = 8;
@@ -86,6 +88,45 @@ int learn_tiles(const mrhweno_problem& p) {
   return learned(p) ? ceil_div_i(ext(p.nx, kFHalo), kLearnW) * ceil_div_i(ext(p.ny, kFHalo), kLearnRows) : 0;
 }
 int strip_cells(const mrhweno_problem& p) { return kBlock / ncomp_of(p); }   /* 2D strip width incl. ring */
+int strip_cols(const mrhweno_problem& p) { return ceil_div_i(p.nx, strip_cells(p) - 2); }
+/* 2D stage strips at height rows, and an upper bound of them at every height
+   strip_rows may choose */
+long long strip_count(const mrhweno_problem& p, int rows) { return (long long)strip_cols(p) * ceil_div_i(p.ny, rows); }
+size_t strip_bound(const mrhweno_problem& p) {
+  return (size_t)(strip_count(p, kMinRows) + std::min<long long>(kFewStrips, strip_count(p, 1)));
+}
+/* Height of the 2D stage strips of a launch over the problems ps: `rows`
+   (0: none set, kDefRows) or less where strips of that height leave the GPU
+   short of work.  A strip of h rows takes h + 2 row steps, one after
+   another, so on a small grid the launch lasts as long as one strip: with a
+   work group to itself a CU does a row step in 4.35 us, two resident ones
+   take 6.6 us a step (15 and 22 characteristic-wise, the same ratio), and a
+   launch costs 10 us besides (all measured).  The height that minimises the
+   rounds of 2 x 256 groups by that rule is taken, the tallest among equals:
+   96 x 96 cells 1 row, 23 us (32 rows: 157); 331 x 257 4 rows, 49 us (159);
+   512 x 384 7 rows, 69 us (158); 1024 x 1024 24 rows, 257 us (318).  From
+   2048 strips on the rounds overlap and the height matters little, so it
+   stays; so does a height the caller set that fills the GPU. */
+int strip_rows(const std::vector<const mrhweno_problem*>& ps, int rows) {
+  const int top = rows > 0 ? rows : kDefRows;
+  auto count = [&](int h) {
+    long long n = 0;
+    for (auto* p : ps) n += strip_count(*p, h);
+    return n;
+  };
+  const long long n0 = count(top);
+  if (n0 >= 4 * 512 || (rows > 0 && n0 >= 512)) return top;
+  int best = top;
+  double bc = -1.0;
+  for (int h = top; h >= 1; --h) {
+    const long long n = count(h), rem = n % 512;
+    if (h < kMinRows && n > kFewStrips) break;   /* the lists are sized for no more */
+    const double cost = (double)(n / 512) * (10.0 + 6.6 * (h + 2)) +
+                        (rem == 0 ? 0.0 : 10.0 + (rem <= 256 ? 4.35 : 6.6) * (h + 2));
+    if (bc < 0.0 || cost < bc) { bc = cost; best = h; }
+  }
+  return best;
+}
 /* rows of a 2D KXRCF work item: 46 (each strip also reconstructs a ring row
    above and below), fewer for grids too small to fill the GPU otherwise */
 int kx_rows(const mrhweno_problem& p) {
@@ -202,10 +243,10 @@ Layout layout(const mrhweno_problem* P, int n) {
     size_t a = ceil_div(plane_of(p), kBlock) + ceil_div((long long)sex(p) * sey(p), kBlock) +
                ceil_div((long long)fex(p) * fey(p), kBlock) + ceil_div(plane_of(p), kBlock);
     if (p.dim == 1) a += ceil_div(p.nx, kFused1);
-    else t2 += (size_t)ceil_div(p.nx, strip_cells(p) - 2) * ceil_div(p.ny, kMinRows) + kx_tiles(p, kKxMinRows);
+    else t2 += 2 * strip_bound(p) + kx_tiles(p, kKxMinRows);   /* 2: strips along a side with data are lower */
     t1 += a;
     tmax = std::max(tmax, a + learn_tiles(p) + kx_tiles(p) +
-                              (p.dim == 2 ? (size_t)ceil_div(p.nx, strip_cells(p) - 2) * ceil_div(p.ny, kMinRows) : 0));
+                              (p.dim == 2 ? strip_bound(p) : 0));
     L.n_tilesl += learn_tiles(p);
     if (learned(p)) L.n_band += (size_t)fex(p) * fey(p);
   }
@@ -309,7 +350,7 @@ struct mrhweno_ctx {
   std::vector<Group> groups;
   std::vector<mr_tile1> h_t1;
   std::vector<mr_tile2> h_t2;
-  int rows2 = 32, grid2 = 0;
+  int rows2 = 0, grid2 = 0;   /* 0: chosen per launch (strip_rows) */
   int kx_rows2 = 0;   /* rows of a 2D KXRCF work item (0: chosen per problem) */
   int nxcd = 1;       /* XCDs of the device (work-list order) */
   /* learned indicator */
@@ -440,11 +481,13 @@ static void build_lists(mrhweno_ctx* c) {
       std::vector<int> order = g.insts;
       std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         return plane_of(c->probs[a]) > plane_of(c->probs[b]); });
+      std::vector<const mrhweno_problem*> ps;
+      for (int q : order) ps.push_back(&c->probs[q]);
+      const int rows = strip_rows(ps, c->rows2);
       for (int q : order) {
         const auto& p = c->probs[q];
         const size_t first = c->h_t2.size();
         const int w = strip_cells(p) - 2;
-        const int rows = std::max(kMinRows, c->rows2);
         const bool lx = side_data(p, 0), rx = side_data(p, 1);
         if (!lx && !rx) {
           for (int y0 = 0; y0 < p.ny; y0 += rows)
@@ -458,7 +501,7 @@ static void build_lists(mrhweno_ctx* c) {
            the rows, so that they finish with the rest of the launch */
         for (int x0 = 0; x0 < p.nx; x0 += w) {
           const bool edge = (lx && x0 - 3 < 0) || (rx && x0 + w + 2 >= p.nx);
-          const int r = edge ? std::max(kMinRows, rows / 2) : rows;
+          const int r = edge ? (rows + 1) / 2 : rows;
           for (int y0 = 0; y0 < p.ny; y0 += r) c->h_t2.push_back(mr_tile2{q, x0, y0, std::min(r, p.ny - y0)});
         }
         xcd_order(c->h_t2, first, c->nxcd);
@@ -723,7 +766,7 @@ mrhweno_status mrhweno_autotune(mrhweno_ctx* c, const int* rows_cand, int n_rows
   bool any2d = false;
   for (auto& g : c->groups) any2d |= g.dim == 2;
   if (!any2d) {
-    if (best_rows) *best_rows = c->rows2;
+    if (best_rows) *best_rows = c->rows2 > 0 ? c->rows2 : kDefRows;
     if (best_grid) *best_grid = c->grid2;
     if (best_ms) *best_ms = 0.0f;
     return MRHWENO_OK;
@@ -786,7 +829,7 @@ mrhweno_status mrhweno_autotune(mrhweno_ctx* c, const int* rows_cand, int n_rows
   mrhweno_status s2 = upload_lists(c);
   if (st == MRHWENO_OK) st = s2;
   if (st == MRHWENO_OK) st = rebuild_graph(c);
-  if (best_rows) *best_rows = c->rows2;
+  if (best_rows) *best_rows = c->rows2 > 0 ? c->rows2 : kDefRows;
   if (best_grid) *best_grid = c->grid2;
   if (best_ms) *best_ms = best;
   return st;
@@ -967,9 +1010,9 @@ static ProbeLists probe_lists(const mrhweno_problem& p, int slot) {
   if (p.dim == 1) {
     for (int s = 0; s < p.nx; s += kBlock - 2) L.t1.push_back(mr_tile1{slot, s, std::min(kBlock - 2, p.nx - s), 0});
   } else {
-    const int w = strip_cells(p) - 2;
-    for (int y0 = 0; y0 < p.ny; y0 += 32)
-      for (int x0 = 0; x0 < p.nx; x0 += w) L.t2.push_back(mr_tile2{slot, x0, y0, std::min(32, p.ny - y0)});
+    const int w = strip_cells(p) - 2, rows = strip_rows({&p}, 0);
+    for (int y0 = 0; y0 < p.ny; y0 += rows)
+      for (int x0 = 0; x0 < p.nx; x0 += w) L.t2.push_back(mr_tile2{slot, x0, y0, std::min(rows, p.ny - y0)});
   }
   L.n_st = (int)L.t1.size() - L.t_st;
   if (lrn) add_learn_tiles(L.t3, slot, p);
