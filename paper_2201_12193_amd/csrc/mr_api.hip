@@ -54,7 +54,8 @@ constexpr int kKxMinRows = 8;
 constexpr int kKxMaxRows = 256; /* tallest height a caller may set */
 constexpr int kKxFill = 512; /* work groups that fill the GPU (256 CUs x 2 resident)    */
 constexpr int kLearnW = 64;     /* learned-indicator work item: 64 columns ...       */
-constexpr int kLearnRows = 32;  /* ... x 32 rows of the extended flag range          */
+constexpr int kLearnRows = 160; /* ... x at most 160 rows of the extended flag range  */
+constexpr int kLearnFill = 512; /* work groups of it that fill the GPU               */
 
 thread_local std::string g_err;
 
@@ -83,9 +84,32 @@ bool side_data(const mrhweno_problem& p, int s) {
   const int bc = s < 2 ? p.bc_x : p.bc_y;
   return bc == MRHWENO_BC_SIDES && (p.side[s].kind == MRHWENO_SIDE_INFLOW || p.side[s].front);
 }
-/* work items of the learned indicator: strips over [-2, n+2)^2 */
-int learn_tiles(const mrhweno_problem& p) {
-  return learned(p) ? ceil_div_i(ext(p.nx, kFHalo), kLearnW) * ceil_div_i(ext(p.ny, kFHalo), kLearnRows) : 0;
+/* work items of the learned indicator: strips over [-2, n+2)^2, `rows` rows
+   each, and an upper bound of them at every height learn_rows may choose */
+long long learn_count(const mrhweno_problem& p, int rows) {
+  return learned(p) ? (long long)ceil_div_i(ext(p.nx, kFHalo), kLearnW) * ceil_div_i(ext(p.ny, kFHalo), rows) : 0;
+}
+size_t learn_bound(const mrhweno_problem& p) {
+  return (size_t)(learn_count(p, 32) + std::min<long long>(2 * kLearnFill, learn_count(p, 4)));
+}
+/* Height of the learned indicator's strips over the problems ps (a multiple
+   of the four rows a step takes): the one that minimises rounds of
+   kLearnFill resident groups times steps, the prologue counted as one more;
+   the tallest among equals.  What matters is a last round that is nearly
+   empty: at 1024 x 1024 cells 32 rows are 561 strips, 97 us, and 36 rows 493
+   strips, 81 us.  Over many rounds the height hardly counts (2048 x 2048:
+   260 to 278 us from 12 to 140 rows). */
+int learn_rows(const std::vector<const mrhweno_problem*>& ps) {
+  int best = kLearnRows;
+  long long bc = -1;
+  for (int r = kLearnRows; r >= 4; r -= 4) {
+    long long n = 0;
+    for (auto* p : ps) n += learn_count(*p, r);
+    if (r < 32 && n > 2 * kLearnFill) break;   /* the lists are sized for no more */
+    const long long cost = ((n + kLearnFill - 1) / kLearnFill) * (r / 4 + 1);
+    if (bc < 0 || cost < bc) { bc = cost; best = r; }
+  }
+  return best;
 }
 int strip_cells(const mrhweno_problem& p) { return kBlock / ncomp_of(p); }   /* 2D strip width incl. ring */
 int strip_cols(const mrhweno_problem& p) { return ceil_div_i(p.nx, strip_cells(p) - 2); }
@@ -245,9 +269,9 @@ Layout layout(const mrhweno_problem* P, int n) {
     if (p.dim == 1) a += ceil_div(p.nx, kFused1);
     else t2 += 2 * strip_bound(p) + kx_tiles(p, kKxMinRows);   /* 2: strips along a side with data are lower */
     t1 += a;
-    tmax = std::max(tmax, a + learn_tiles(p) + kx_tiles(p) +
+    tmax = std::max(tmax, a + (learned(p) ? learn_bound(p) : 0) + kx_tiles(p) +
                               (p.dim == 2 ? strip_bound(p) : 0));
-    L.n_tilesl += learn_tiles(p);
+    if (learned(p)) L.n_tilesl += learn_bound(p);
     if (learned(p)) L.n_band += (size_t)fex(p) * fey(p);
   }
   L.n_tiles1 = t1;
@@ -295,7 +319,7 @@ struct Group {
   int t_st2 = 0, n_st2 = 0, t_kx = 0, n_kx = 0, t_tvb = 0, n_tvb = 0;
 };
 
-/* learned-indicator work items of one instance (instance id `slot`) */
+/* KXRCF work items of one instance (instance id `slot`) */
 void add_kx_tiles(std::vector<mr_tile2>& v, int slot, const mrhweno_problem& p, int rows_set = 0) {
   const int rows = rows_set > 0 ? rows_set : kx_rows(p);
   for (int y0 = -kFHalo; y0 < p.ny + kFHalo; y0 += rows)
@@ -328,10 +352,11 @@ void xcd_order(std::vector<mr_tile2>& v, size_t begin, int nxcd) {
   }
 }
 
-void add_learn_tiles(std::vector<mr_tile2>& v, int slot, const mrhweno_problem& p) {
-  for (int y0 = -kFHalo; y0 < p.ny + kFHalo; y0 += kLearnRows)
+/* learned-indicator work items of one instance */
+void add_learn_tiles(std::vector<mr_tile2>& v, int slot, const mrhweno_problem& p, int rows) {
+  for (int y0 = -kFHalo; y0 < p.ny + kFHalo; y0 += rows)
     for (int x0 = -kFHalo; x0 < p.nx + kFHalo; x0 += kLearnW)
-      v.push_back(mr_tile2{slot, x0, y0, std::min(kLearnRows, p.ny + kFHalo - y0)});
+      v.push_back(mr_tile2{slot, x0, y0, std::min(rows, p.ny + kFHalo - y0)});
 }
 
 }  // namespace
@@ -676,11 +701,13 @@ mrhweno_status mrhweno_create(const mrhweno_problem* probs, int n, void* const* 
     c->band = (mr_band*)(c->ws + c->L.band);
     c->tl = (mr_tile2*)(c->ws + c->L.tilesl);
     std::vector<mr_tile2> tl;
+    std::vector<const mrhweno_problem*> ps;
     for (int q = 0; q < n; ++q)
-      if (learned(probs[q])) {
-        add_learn_tiles(tl, q, probs[q]);
-        c->learned_bp |= probs[q].beta_on;
-      }
+      if (learned(probs[q])) ps.push_back(&probs[q]);
+    for (auto* p : ps) {
+      add_learn_tiles(tl, (int)(p - probs), *p, learn_rows(ps));
+      c->learned_bp |= p->beta_on;
+    }
     c->n_tl = (int)tl.size();
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess &&
@@ -1015,7 +1042,7 @@ static ProbeLists probe_lists(const mrhweno_problem& p, int slot) {
       for (int x0 = 0; x0 < p.nx; x0 += w) L.t2.push_back(mr_tile2{slot, x0, y0, std::min(rows, p.ny - y0)});
   }
   L.n_st = (int)L.t1.size() - L.t_st;
-  if (lrn) add_learn_tiles(L.t3, slot, p);
+  if (lrn) add_learn_tiles(L.t3, slot, p, learn_rows({&p}));
   if (L.kx2) add_kx_tiles(L.t3, slot, p);
   return L;
 }

@@ -219,6 +219,31 @@ MR_INL double mr_ld(const mr_grid& g, int c, int m, int i, int j) {
   return v;
 }
 
+/* the 3 x 3 stencil of component c around (x, y): averages u, first moments
+ * v, w (label order).  Away from the grid's edges (and the step) the loads
+ * are one address and fixed row offsets; the ghost rules of mr_ld take about
+ * twenty instructions a value, more than Step 1 takes on the whole stencil. */
+MR_INL void mr2_stencil(const mr_grid& g, int c, int x, int y, double u[9], double v[9], double w[9]) {
+  if (x >= 1 && x < g.nx - 1 && y >= 1 && y < g.ny - 1 && !(g.I && g.I->stepj > 0)) {
+    const MR_GLB double* a = g.U + (long long)(c * 3) * g.P + (long long)(y - 1) * g.nx + (x - 1);
+#pragma unroll
+    for (int l = 0; l < 9; ++l) {
+      const MR_GLB double* q = a + (l / 3) * (long long)g.nx + l % 3;
+      u[l] = q[0];
+      v[l] = q[g.P];
+      w[l] = q[2 * g.P];
+    }
+    return;
+  }
+#pragma unroll
+  for (int l = 0; l < 9; ++l) {
+    const int i = x + l % 3 - 1, j = y + l / 3 - 1;
+    u[l] = mr_ld(g, c, 0, i, j);
+    v[l] = mr_ld(g, c, 1, i, j);
+    w[l] = mr_ld(g, c, 2, i, j);
+  }
+}
+
 /* Step 1 of a 1D cell for its NC components from the three-cell stencil
  * (averages um, u0, up and first moments vm, v0, vp per component):
  * component by component, or, for Euler with I.charwise, on the
@@ -357,17 +382,13 @@ MR_INL void mr2_cell_values(const mr_grid& g, const mr_inst& I, const MR_GLB uns
                             int c, int x, int y, double out[16], double* ue, double* ve, double* we) {
   double u[9], v[9], w[9];
   int fs[9];
+  mr2_stencil(g, c, x, y, u, v, w);
+  fs[4] = mr_flag(fl, I.fex, I.fey, I.fhalo, x, y);
+  if (fs[4]) {
 #pragma unroll
-  for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-    for (int dx = -1; dx <= 1; ++dx) {
-      const int l = (dx + 1) + 3 * (dy + 1);
-      u[l] = mr_ld(g, c, 0, x + dx, y + dy);
-      v[l] = mr_ld(g, c, 1, x + dx, y + dy);
-      w[l] = mr_ld(g, c, 2, x + dx, y + dy);
-      fs[l] = mr_flag(fl, I.fex, I.fey, I.fhalo, x + dx, y + dy);
-    }
-  if (fs[4]) mr2_modify_stencil(g, c, x, y, fs, v, w);
+    for (int l = 0; l < 9; ++l) fs[l] = mr_flag(fl, I.fex, I.fey, I.fhalo, x + l % 3 - 1, y + l / 3 - 1);
+    mr2_modify_stencil(g, c, x, y, fs, v, w);
+  }
   *ue = u[4];
   *ve = v[4];
   *we = w[4];
@@ -401,11 +422,7 @@ MR_INL void mr2_cell_values_ch(const mr_grid& g, const mr_inst& I, const MR_GLB 
     for (int l = 0; l < 9; ++l) { fu[l] = 0.0; fv[l] = 0.0; fw[l] = 0.0; }
     for (int c = 0; c < 4; ++c) {
       double u[9], v[9], ww[9];
-      for (int l = 0; l < 9; ++l) {
-        u[l] = mr_ld(g, c, 0, x + l % 3 - 1, y + l / 3 - 1);
-        v[l] = mr_ld(g, c, 1, x + l % 3 - 1, y + l / 3 - 1);
-        ww[l] = mr_ld(g, c, 2, x + l % 3 - 1, y + l / 3 - 1);
-      }
+      mr2_stencil(g, c, x, y, u, v, ww);
       if (fs[4]) mr2_modify_stencil(g, c, x, y, fs, v, ww);
       for (int l = 0; l < 9; ++l) { fu[l] += lk[c] * u[l]; fv[l] += lk[c] * v[l]; fw[l] += lk[c] * ww[l]; }
     }
@@ -433,13 +450,7 @@ MR_INL void mr2_face_summary(const mr_grid& g, const mr_inst& I, int i, int j, d
 #pragma unroll 1
   for (int c = 0; c < ncomp; ++c) {
     double u[9], v[9], w[9], r[16];
-#pragma unroll
-    for (int l = 0; l < 9; ++l) {
-      const int dx = l % 3 - 1, dy = l / 3 - 1;
-      u[l] = mr_ld(g, c, 0, i + dx, j + dy);
-      v[l] = mr_ld(g, c, 1, i + dx, j + dy);
-      w[l] = mr_ld(g, c, 2, i + dx, j + dy);
-    }
+    mr2_stencil(g, c, i, j, u, v, w);
     mr_recon2d<BP>(u, v, w, I.W, r);
     if (c == 0) {
 #pragma unroll

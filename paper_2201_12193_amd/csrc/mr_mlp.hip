@@ -21,6 +21,7 @@
  *   s = 75, g = 0: log2(h)/16;   every other index is 0.
  * This order lets lane group g of the MFMA operand read window row g - 2 at
  * offsets fixed at compile time. */
+#define MR_KT_IN_LDS 1
 #include <algorithm>
 
 #include "mr_common.h"
@@ -107,22 +108,45 @@ __global__ __launch_bounds__(MR_BLOCK) void k_features(const mr_inst* insts, int
 /* Work item: a strip of 64 columns x `rows` rows of the extended flag range
  * [-2, n+2)^2.  The four waves of a work group take four consecutive rows
  * per sweep step; the moments of rows y-2 .. y+5 sit in an LDS ring of
- * eight FP32 rows.  Per wave and step, 64 cells in four groups of 16:
+ * eight FP32 rows, the next four rows' loads in flight while a step
+ * computes.  Per wave and step, 64 cells in four groups of 16 (group gi:
+ * cells 4 r + gi, r < 16, so that the 5-column windows of a lane's four cells
+ * are eight consecutive staged columns, two 16-byte LDS reads per plane and
+ * row):
  *   layer 1: h1 (64 x 16) = W1 (64 x 320) X (320 x 16), 40 MFMAs;
  *   layer 2: h2 = W2 relu(h1 + b1), 8 MFMAs, with the contraction order
  *            permuted alike on both operands so that the layer-1
  *            accumulators serve as the B operand without a transpose;
  *   layer 3: a dot product reduced across the four lane groups.
+ * What bounds it: instruction issue.  Of the time at 2048 x 2048 the 304
+ * multiplications that scale a wave's features and their 152 conversions
+ * take 20 %, the matrix instructions of layer 1 18 %, staging 12 %, those of
+ * layer 2 4 %, the norms 3 %; HBM would allow 100 us.  Deeper rings with one
+ * barrier a step or none, eight-wave groups and raised wave priorities
+ * measured the same or slower.  118 -> 77 us at 1024 x 1024; 333 -> 295
+ * us at 2048 x 2048 with the fallback below (windows read 16 bytes at a
+ * time, loads a step ahead, vector work behind each matrix instruction, the
+ * undecided cells gathered in LDS, the strips' height).
  * Lane i of the MFMA holds A[i%16][8(i/16)+j], B[8(i/16)+j][i%16] (j < 8)
  * and receives D[4(i/16)+j][i%16] (j < 4). */
 #define MR_LW 64                       /* cells per strip row              */
 #define MR_LCOLS (MR_LW + 4)           /* staged columns                   */
-#define MR_LRS 80                      /* LDS row stride (floats)          */
+#define MR_LRS MR_LCOLS                /* LDS row stride (floats)          */
 #define MR_LPL (8 * MR_LRS + 16)       /* LDS plane stride (floats)        */
-struct mr_learn_lds {
+#define MR_LBAND 1408                  /* undecided cells held in LDS      */
+struct __attribute__((aligned(16))) mr_learn_lds {
   mr_learn_w w;
   float mom[12 * MR_LPL];
+  int nband, base;                     /* cells in the list; its place in the band */
+  unsigned short band[MR_LBAND];       /* 64 (row in the strip) + column    */
 };
+
+/* eight consecutive floats of LDS, 16-byte aligned */
+MR_INL void mr_ld8f(const float* p, float v[8]) {
+  const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
+  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+  v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
 
 __global__ __launch_bounds__(MR_BLOCK, 2) void k2_learned(const mr_inst* __restrict__ insts, const mr_tile2* __restrict__ tiles, int ntiles,
                                                          int stage, const mr_learn_w* wg, mr_band* band, int* cnt) {
@@ -151,27 +175,27 @@ __global__ __launch_bounds__(MR_BLOCK, 2) void k2_learned(const mr_inst* __restr
     const int xend = I.nx + fh;
     const float gam = (float)I.gam, lh = (float)(log2(I.dx) * (1.0 / 16.0));
     const float blo = (float)I.band_lo, bhi = (float)I.band_hi;
-    /* staging of four rows: every thread issues its loads together (into
-       registers) so that their latencies overlap, then converts and stores;
-       first moments of transmissive ghosts read as zero, reflective ghosts
-       flip the moments mr_refl_flip names */
+    /* staging of four rows: every thread issues its loads together, into
+       registers; they are converted and stored later.  First moments of
+       transmissive ghosts read as zero, reflective ghosts flip the moments
+       mr_refl_flip names; strips and rows without ghosts skip those rules */
     int kx = 0;
     const int ii = mr_fold(xs + scol, I.nx, I.bcx, &kx);
-    const bool zx = sm != 0 && kx == 1;
-    const MR_GLB double* ub = gr.U + (long long)sm * I.plane + ii;
+    const bool xplain = (xs >= 0 || (I.bcx & 3) == 0) && (xs + MR_LCOLS <= I.nx || ((I.bcx >> 2) & 3) == 0);
+    const long long P = I.plane;
+    const MR_GLB double* ub = gr.U + (long long)sm * P + ii;
     double pf[16];
+    int kys = 0;   /* y ghost kind of row rr in bits 2 rr, 2 rr + 1 (uniform) */
     auto fetch = [&](int row0) {
-      if (!stager) return;
+      kys = 0;
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
         int ky = 0;
-        const int jj = mr_fold(row0 + rr, I.ny, I.bcy, &ky);
-        const bool zero = zx || (sm != 0 && ky == 1);
+        const long long jj = (long long)mr_fold(row0 + rr, I.ny, I.bcy, &ky) * I.nx;
+        kys |= ky << (2 * rr);
+        if (stager) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const double v = ub[(3 * c) * I.plane + (long long)jj * I.nx];
-          const bool neg = (kx == 2 && mr_refl_flip(c, sm, 0)) != (ky == 2 && mr_refl_flip(c, sm, 1));
-          pf[4 * rr + c] = zero ? 0.0 : (neg ? -v : v);
+          for (int c = 0; c < 4; ++c) pf[4 * rr + c] = (ub + (3 * c) * P)[jj];
         }
       }
     };
@@ -180,29 +204,49 @@ __global__ __launch_bounds__(MR_BLOCK, 2) void k2_learned(const mr_inst* __restr
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
         const int slot = (row0 + rr - ylo + 2) & 7;
+        float* d = sh.mom + sm * MR_LPL + slot * MR_LRS + scol;
+        if (xplain && kys == 0) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          sh.mom[(3 * c + sm) * MR_LPL + slot * MR_LRS + scol] = (float)pf[4 * rr + c];
+          for (int c = 0; c < 4; ++c) d[3 * c * MR_LPL] = (float)pf[4 * rr + c];
+        } else {
+          const int ky = (kys >> (2 * rr)) & 3;
+          const bool zero = sm != 0 && (kx == 1 || ky == 1);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const bool neg = (kx == 2 && mr_refl_flip(c, sm, 0)) != (ky == 2 && mr_refl_flip(c, sm, 1));
+            const double v = pf[4 * rr + c];
+            d[3 * c * MR_LPL] = (float)(zero ? 0.0 : (neg ? -v : v));
+          }
+        }
       }
     };
     __syncthreads();
+    if (tid == 0) sh.nband = 0;
     fetch(ylo - 2);
     store(ylo - 2);   /* rows ylo-2 .. ylo+1 */
+    fetch(ylo + 2);
+    store(ylo + 2);   /* rows ylo+2 .. ylo+5 */
+    __syncthreads();
     for (int y = ylo; y < yhi; y += 4) {
-      fetch(y + 2);
-      store(y + 2);   /* rows y+2 .. y+5 */
-      __syncthreads();
+      const bool more = y + 4 < yhi;
+      if (more) fetch(y + 6);   /* the rows that replace y-2 .. y+1 */
       const int Y = y + wv;
-      /* LDS bases: centre row, the lane group's window row (wy = g - 2),
-         and window row wy = 2 of component g */
-      const int bc = ((Y - ylo + 2) & 7) * MR_LRS + r + 2;
-      const int bo = ((Y - ylo + g) & 7) * MR_LRS + r + 2;
-      const int b2 = ((Y - ylo + 4) & 7) * MR_LRS + r + 2 + 3 * g * MR_LPL;
+      /* LDS bases (16-byte aligned): centre row, the lane group's window row
+         (wy = g - 2), and window row wy = 2 of component g */
+      const int bc = ((Y - ylo + 2) & 7) * MR_LRS + 4 * r;
+      const int bo = ((Y - ylo + g) & 7) * MR_LRS + 4 * r;
+      const int b2 = ((Y - ylo + 4) & 7) * MR_LRS + 4 * r + 3 * g * MR_LPL;
       float sc[4][4], cs[4][4], scg[4], csg[4];
+      {
+        float ctr[4][8];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) mr_ld8f(&sh.mom[3 * c * MR_LPL + bc], ctr[c]);
+#pragma unroll
+        for (int gi = 0; gi < 4; ++gi)
+          mr_feat_norm(ctr[0][gi + 2], ctr[1][gi + 2], ctr[2][gi + 2], ctr[3][gi + 2], gam, sc[gi], cs[gi]);
+      }
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi) {
-        mr_feat_norm(sh.mom[0 * MR_LPL + bc + 16 * gi], sh.mom[3 * MR_LPL + bc + 16 * gi],
-                     sh.mom[6 * MR_LPL + bc + 16 * gi], sh.mom[9 * MR_LPL + bc + 16 * gi], gam, sc[gi], cs[gi]);
         scg[gi] = g == 0 ? sc[gi][0] : (g == 3 ? sc[gi][3] : sc[gi][1]);
         csg[gi] = g == 0 ? cs[gi][0] : (g == 1 ? cs[gi][1] : (g == 2 ? cs[gi][2] : cs[gi][3]));
       }
@@ -218,78 +262,70 @@ __global__ __launch_bounds__(MR_BLOCK, 2) void k2_learned(const mr_inst* __restr
 #pragma unroll
         for (int gi = 0; gi < 4; ++gi) h[gi][m] = f32x4{bb.x, bb.y, bb.z, bb.w};
       }
-      /* raw moment of slot s for cell group gi (LDS), 0 for the other slots */
-      auto raw = [&](int s, int gi) -> float {
-        if (s < 60) {
-          const int c = s / 15, m = (s / 5) % 3, wx = s % 5 - 2;
-          return sh.mom[(3 * c + m) * MR_LPL + bo + 16 * gi + wx];
-        }
-        if (s < 75) {
-          const int m = (s - 60) / 5, wx = (s - 60) % 5 - 2;
-          return sh.mom[m * MR_LPL + b2 + 16 * gi + wx];
-        }
-        return 0.0f;
+      /* planes of the window, five slots each: plane p < 12 moment p of the
+         lane's own row, p = 12 .. 14 moment p - 12 of component g in row
+         wy = 2 */
+      float rw[15][8];
+      auto plane = [&](int p) { mr_ld8f(&sh.mom[p < 12 ? p * MR_LPL + bo : (p - 12) * MR_LPL + b2], rw[p]); };
+      auto feat = [&](int s, int gi) -> float {
+        if (s < 60) return mr_feat_val(rw[s / 5][s % 5 + gi], (s / 5) % 3, cs[gi][s / 15], sc[gi][s / 15]);
+        if (s < 75) return mr_feat_val(rw[s / 5][s % 5 + gi], (s - 60) / 5, csg[gi], scg[gi]);
+        return s == 75 && g == 0 ? lh : 0.0f;
       };
-      /* software pipeline over (contraction block, pair of cell groups): the
-         LDS reads of the next step are issued before the current step's
-         conversions and MFMAs, so their latency is hidden */
-      float nxt[2][8];
+      /* layer 1, pipelined by hand: behind each matrix instruction the vector
+         instructions of two features of the next operand, which run while it
+         occupies the matrix core (in the compiler's order, four matrix
+         instructions and then twelve vector ones, the two hardly overlap);
+         weights and planes are read a contraction block ahead */
+      bf16x8 a[2][4], b;
 #pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2)
+      for (int m = 0; m < 4; ++m) a[0][m] = W1[m * 64 + lane];
+      plane(0);
+      plane(1);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) nxt[h2][j] = raw(j, h2);
+      for (int j = 0; j < 8; ++j) b[j] = (__bf16)feat(j, 0);
 #pragma unroll
       for (int kb = 0; kb < MR_KP / 32; ++kb) {
-        bf16x8 a[4];
+        if (kb + 1 < MR_KP / 32) {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) a[m] = W1[(kb * 4 + m) * 64 + lane];
+          for (int m = 0; m < 4; ++m) a[(kb + 1) & 1][m] = W1[((kb + 1) * 4 + m) * 64 + lane];
 #pragma unroll
-        for (int pr = 0; pr < 2; ++pr) {
-          float cur[2][8];
+          for (int p = 2; p < 15; ++p)
+            if (p > (8 * kb + 7) / 5 && p <= (8 * kb + 15) / 5) plane(p);
+        }
 #pragma unroll
-          for (int h2 = 0; h2 < 2; ++h2)
+        for (int gi = 0; gi < 4; ++gi) {
+          const int nk = kb + (gi == 3), ng = (gi + 1) & 3;
+          bf16x8 bn = {};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) cur[h2][j] = nxt[h2][j];
-          const int nkb = pr == 1 ? kb + 1 : kb, npr = pr == 1 ? 0 : 1;
-          if (nkb < MR_KP / 32) {
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-              for (int j = 0; j < 8; ++j) nxt[h2][j] = raw(8 * nkb + j, 2 * npr + h2);
-          }
-#pragma unroll
-          for (int h2 = 0; h2 < 2; ++h2) {
-            const int gi = 2 * pr + h2;
-            bf16x8 b;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const int s = 8 * kb + j;
-              float v = 0.0f;
-              if (s < 60) {
-                const int c = s / 15, m = (s / 5) % 3;
-                v = mr_feat_val(cur[h2][j], m, cs[gi][c], sc[gi][c]);
-              } else if (s < 75) {
-                v = mr_feat_val(cur[h2][j], (s - 60) / 5, csg[gi], scg[gi]);
-              } else if (s == 75) {
-                v = g == 0 ? lh : 0.0f;
-              }
-              b[j] = (__bf16)v;
+          for (int m = 0; m < 4; ++m) {
+            h[gi][m] = mr_mfma(a[kb & 1][m], b, h[gi][m]);
+            if (nk < MR_KP / 32) {
+              const bf16x2 f2 = __builtin_convertvector(f32x2{feat(8 * nk + 2 * m, ng), feat(8 * nk + 2 * m + 1, ng)}, bf16x2);
+              bn[2 * m] = f2[0];
+              bn[2 * m + 1] = f2[1];
             }
-#pragma unroll
-            for (int m = 0; m < 4; ++m) h[gi][m] = mr_mfma(a[m], b, h[gi][m]);
+            __builtin_amdgcn_sched_barrier(0);
           }
+          b = bn;
         }
       }
       /* layer 2 and 3; this lane holds hidden units 16m + 4g + j */
+      bf16x8 a2[2][4];
+      float4 b2v[4], w3v[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        a2[0][m] = W2[m * 64 + lane];
+        a2[1][m] = W2[(4 + m) * 64 + lane];
+        b2v[m] = b2v4[4 * m + g];
+        w3v[m] = w3v4[4 * m + g];
+      }
       float z[4];
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi) {
         f32x4 o[4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const float4 bb = b2v4[4 * m + g];
-          o[m] = f32x4{bb.x, bb.y, bb.z, bb.w};
-        }
+        for (int m = 0; m < 4; ++m) o[m] = f32x4{b2v[m].x, b2v[m].y, b2v[m].z, b2v[m].w};
 #pragma unroll
         for (int kb2 = 0; kb2 < 2; ++kb2) {
           const f32x4 x = h[gi][2 * kb2], y = h[gi][2 * kb2 + 1];
@@ -297,33 +333,32 @@ __global__ __launch_bounds__(MR_BLOCK, 2) void k2_learned(const mr_inst* __restr
           const bf16x2 p1 = __builtin_convertvector(f32x2{x[2], x[3]}, bf16x2);
           const bf16x2 p2 = __builtin_convertvector(f32x2{y[0], y[1]}, bf16x2);
           const bf16x2 p3 = __builtin_convertvector(f32x2{y[2], y[3]}, bf16x2);
-          bf16x8 b = {p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
+          bf16x8 bb = {p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
           /* ReLU after the rounding (rounding keeps the sign): a negative
              BF16 is a negative int16, so a packed integer max with 0 clears
              it, two values per instruction */
-          b = __builtin_bit_cast(bf16x8, __builtin_elementwise_max(__builtin_bit_cast(i16x8, b), i16x8{}));
+          bb = __builtin_bit_cast(bf16x8, __builtin_elementwise_max(__builtin_bit_cast(i16x8, bb), i16x8{}));
 #pragma unroll
-          for (int m = 0; m < 4; ++m) o[m] = mr_mfma(W2[(kb2 * 4 + m) * 64 + lane], b, o[m]);
+          for (int m = 0; m < 4; ++m) o[m] = mr_mfma(a2[kb2][m], bb, o[m]);
         }
         float zp = 0.f;
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
-          const float4 ww = w3v4[4 * m + g];
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             const float v = o[m][j];
             /* ReLU on the bit pattern: a negative float is a negative int32 */
-            zp += __builtin_bit_cast(float, max(__builtin_bit_cast(int, v), 0)) * (&ww.x)[j];
+            zp += __builtin_bit_cast(float, max(__builtin_bit_cast(int, v), 0)) * (&w3v[m].x)[j];
           }
         }
         zp += __shfl_xor(zp, 16);
         zp += __shfl_xor(zp, 32);
         z[gi] = zp + sh.w.b3;
       }
-      /* lane L decides cell x0 + L of row Y */
+      /* lane (r, g) decides cell x0 + 4 r + g of row Y */
       const float zz = g == 0 ? z[0] : (g == 1 ? z[1] : (g == 2 ? z[2] : z[3]));
       const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-zz));
-      const int x = tl.x0 + lane;
+      const int x = tl.x0 + 4 * r + g;
       const bool valid = Y < yhi && x < xend;
       const unsigned char f = sg > bhi ? 1 : (sg < blo ? 0 : 2);
       const long long e = (long long)(Y + fh) * fex + (x + fh);
@@ -331,22 +366,42 @@ __global__ __launch_bounds__(MR_BLOCK, 2) void k2_learned(const mr_inst* __restr
       const unsigned long long bm = __ballot(valid && f == 2);
       if (bm) {
         int base = 0;
-        if (lane == 0) base = atomicAdd(&cnt[stage], __popcll(bm));
+        if (lane == 0) base = atomicAdd(&sh.nband, __popcll(bm));
         base = __shfl(base, 0);
-        if (valid && f == 2) {
-          const int pre = __popcll(bm & ((1ull << lane) - 1ull));
-          band[base + pre] = mr_band{tl.inst, (int)e};
-        }
+        if (valid && f == 2)
+          sh.band[base + __popcll(bm & ((1ull << lane) - 1ull))] = (unsigned short)(64 * (Y - ylo) + 4 * r + g);
       }
-      __syncthreads();
+      __syncthreads();   /* rows y-2 .. y+1 are consumed, the list is whole */
+      /* the list goes out when the next step may not fit, and at the end: one
+         global atomic a strip, not one (and its round trip) a wave and row */
+      if (!more || sh.nband > MR_LBAND - 4 * MR_LW) {
+        const int n = sh.nband;
+        if (tid == 0 && n > 0) sh.base = atomicAdd(&cnt[stage], n);
+        __syncthreads();
+        for (int k = tid; k < n; k += MR_BLOCK) {
+          const int b = sh.band[k];
+          band[sh.base + k] = mr_band{tl.inst, (int)((long long)(ylo + b / 64 + fh) * fex + (tl.x0 + b % 64 + fh))};
+        }
+        if (tid == 0) sh.nband = 0;
+      }
+      if (more) {
+        store(y + 6);
+        __syncthreads();
+      }
     }
   }
 }
 
 /* KXRCF for the cells the network left undecided (band list, count
- * cnt[stage]) in one pass: five threads per band cell compute the face data
- * (mr2_face_summary) of the cell and of its four neighbours, and the first
- * of them evaluates eq. (KXRCF_) on them as the fused indicator kernel does.
+ * cnt[stage]) in one pass: fifteen threads per band cell reconstruct the
+ * density and the momenta of the cell and of its four neighbours, five of
+ * them form the face data (as mr2_face_summary), and the first evaluates eq.
+ * (KXRCF_) on it as the fused indicator kernel does.  The list is short
+ * (thousands of cells), so the launch lasts as long as one group's chain of
+ * loads and Step 1: 21 -> 13 us at 1024 x 1024 with the components on three
+ * threads, where one took them in turn, and the constant table in LDS.
+ * (Deciding the velocities' signs from bounds first, five threads a cell,
+ * makes the chain longer: 16 us.)
  * One launch per smoothness-indicator variant; each skips the other's cells.
  * The learned indicator takes no per-side boundary data (the library
  * rejects the combination), so its grids carry no instance for prescribed
@@ -354,17 +409,18 @@ __global__ __launch_bounds__(MR_BLOCK, 2) void k2_learned(const mr_inst* __restr
 template <bool BP>
 __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k_fb_direct(const mr_inst* __restrict__ insts, const mr_band* band, const int* cnt,
                                                               int stage) {
-#pragma clang fp contract(off)
-  constexpr int PB = MR_BLOCK / 5;   /* band cells per block pass */
-  __shared__ double fs[PB][5][9];
+  mr_kt_fill();
+  constexpr int PB = MR_BLOCK / 15;   /* band cells per block pass */
+  __shared__ double pr[PB][5][12];    /* density at points 0,4,8,12 | 3,7,11,15 | 1,2,13,14 */
+  __shared__ double pm[PB][5][2][8];  /* x momentum left | right, y momentum bottom | top   */
+  __shared__ double fs[PB][5][9];     /* face data (mr2_face_summary)                       */
   const int n = cnt[stage];
-  const int tid = threadIdx.x, cb = tid / 5, d = tid % 5;
+  const int tid = threadIdx.x, cb = tid / 15, d = (tid % 15) / 3, c = tid % 3;
   for (int base = blockIdx.x * PB; base < n; base += gridDim.x * PB) {
     const int k = base + cb;
-    const bool act = tid < 5 * PB && k < n;
     mr_band b{0, 0};
     bool mine = false;
-    if (act) {
+    if (tid < 15 * PB && k < n) {
       b = band[k];
       const mr_inst& I = insts[b.inst];
       mine = (I.beta_on != 0) == BP;
@@ -372,14 +428,56 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k_fb_direct(const mr_inst* __
         const int i = b.e % I.fex - I.fhalo, j = b.e / I.fex - I.fhalo;
         const int di = d == 1 ? -1 : (d == 2 ? 1 : 0), dj = d == 3 ? -1 : (d == 4 ? 1 : 0);
         const mr_grid g{mr_gp(stage < 3 ? I.p_in[stage] : I.buf[0]), I.plane, I.nx, I.ny, I.bcx, I.bcy, 3, nullptr, 0.0};
-        double f[9];
-        mr2_face_summary<BP>(g, I, i + di, j + dj, f);
+        double u[9], v[9], w[9], r[16];
+        mr2_stencil(g, c, i + di, j + dj, u, v, w);
+        mr_recon2d<BP>(u, v, w, I.W, r);
+        if (c == 0) {
+          double sl = 0.0, sr = 0.0, sb = 0.0, st = 0.0, nrm = 0.0;
 #pragma unroll
-        for (int q = 0; q < 9; ++q) fs[cb][d][q] = f[q];
+          for (int m = 0; m < 4; ++m) {
+            sl += glw(m) * r[0 + 4 * m];
+            sr += glw(m) * r[3 + 4 * m];
+            sb += glw(m) * r[m];
+            st += glw(m) * r[12 + m];
+            pr[cb][d][m] = r[4 * m];
+            pr[cb][d][4 + m] = r[3 + 4 * m];
+          }
+          pr[cb][d][8] = r[1]; pr[cb][d][9] = r[2]; pr[cb][d][10] = r[13]; pr[cb][d][11] = r[14];
+#pragma unroll
+          for (int q = 0; q < 16; ++q) nrm = fmax(nrm, fabs(r[q]));
+          fs[cb][d][0] = sl; fs[cb][d][1] = sr; fs[cb][d][2] = sb; fs[cb][d][3] = st; fs[cb][d][8] = nrm;
+        } else {
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            pm[cb][d][c - 1][m] = c == 1 ? r[4 * m] : r[m];
+            pm[cb][d][c - 1][4 + m] = c == 1 ? r[3 + 4 * m] : r[12 + m];
+          }
+        }
       }
     }
     __syncthreads();
-    if (mine && d == 0) {
+    if (mine && c == 0) {
+      const double* q = pr[cb][d];
+      const double* mx = pm[cb][d][0];
+      const double* my = pm[cb][d][1];
+      double irl[4], irr[4], irm[4];
+      mr_recip4(q[0], q[1], q[2], q[3], irl);
+      mr_recip4(q[4], q[5], q[6], q[7], irr);
+      mr_recip4(q[8], q[9], q[10], q[11], irm);
+      double vl = 0.0, vr = 0.0;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        vl += glw(m) * (mx[m] * irl[m]);
+        vr += glw(m) * (mx[4 + m] * irr[m]);
+      }
+      fs[cb][d][4] = vl;
+      fs[cb][d][5] = vr;
+      fs[cb][d][6] = glw(0) * (my[0] * irl[0]) + glw(1) * (my[1] * irm[0]) + glw(2) * (my[2] * irm[1]) + glw(3) * (my[3] * irr[0]);
+      fs[cb][d][7] = glw(0) * (my[4] * irl[3]) + glw(1) * (my[5] * irm[2]) + glw(2) * (my[6] * irm[3]) + glw(3) * (my[7] * irr[3]);
+    }
+    __syncthreads();
+    if (mine && c == 0 && d == 0) {
+#pragma clang fp contract(off)
       const mr_inst& I = insts[b.inst];
       MR_GLB unsigned char* fl = mr_gp(I.flags[(stage == 0 || stage == 3) ? 0 : 1]);
       const int i = b.e % I.fex - I.fhalo, j = b.e / I.fex - I.fhalo;
