@@ -291,7 +291,7 @@ mrhweno_status mrhweno_autotune(mrhweno_ctx* ctx, const int* rows_cand, int n_ro
                                 int* best_rows, int* best_grid, float* best_ms);
 
 /* Flag rows per work item of the 2D KXRCF pass (eq. (KXRCF_), Step 2.1):
- * 0 = the height chosen per problem from its size (the default), else a
+ * 0 = the height chosen by size (the default; low strips on small grids), else a
  * value in [8, 256]; each work item covers 62 flag columns.  The flags do
  * not depend on it.  Synchronises the context's stream. */
 mrhweno_status mrhweno_set_indicator_launch(mrhweno_ctx* ctx, int rows);

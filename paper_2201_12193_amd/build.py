@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmrhweno.so")
-SOURCES = ["mr_kernels.hip", "mr_stage2d.hip", "mr_kxrcf2d.hip", "mr_mlp.hip", "mr_api.hip"]
+SOURCES = ["mr_kernels.hip", "mr_stage2d.hip", "mr_kxrcf2d.hip", "mr_kxrcf2w.hip", "mr_mlp.hip", "mr_api.hip"]
 # per-file code generation options: the 2D stage kernel runs at a fixed two
 # waves per SIMD (LDS-bound), so its instructions are scheduled for
 # instruction-level parallelism rather than for occupancy (measured ~2%

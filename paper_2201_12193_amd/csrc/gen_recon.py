@@ -422,6 +422,34 @@ def emit_2d(lines):
     lines.append(f"  /* {total_terms} non-zero map entries after the parity split */")
     lines.append("}")
 
+    # ---- how far q_l may be from the centre average at a face point ----
+    # q_l - u_5 is a sum over the stencil data; per group of data that the
+    # symmetries exchange, the largest coefficient at any face point
+    nodes = [-0.5, -0.2236067977499790, 0.2236067977499790, 0.5]
+
+    def group(t, lb):
+        dx, dy = lab_off(lb)
+        if t == 0:
+            return "UE" if dx == 0 or dy == 0 else "UC"
+        return "M0" if dx == 0 and dy == 0 else ("ME" if dx == 0 or dy == 0 else "MC")
+    lines.append("/* largest |coefficient| of a datum in q_l - u_5 at the face points (rounded up):")
+    lines.append("   UE, UC: averages of the edge and corner neighbours minus u_5; M0, ME, MC:")
+    lines.append("   first moments of the cell, its edge and its corner neighbours */")
+    for l in (2, 3, 4):
+        Mn = [[float(z) for z in row] for row in lsq_map_2d(nco[l], conds[l]).tolist()]
+        big = dict(UE=0.0, UC=0.0, M0=0.0, ME=0.0, MC=0.0)
+        for i, x in enumerate(nodes):
+            for j, y in enumerate(nodes):
+                if i not in (0, 3) and j not in (0, 3):
+                    continue
+                ev = [x ** a * y ** b for a, b in MON[:nco[l]]]
+                for k, (t, lb) in enumerate(conds[l]):
+                    if (t, lb) != (0, 5):
+                        g = group(t, lb)
+                        big[g] = max(big[g], abs(sum(e * Mn[p][k] for p, e in enumerate(ev))))
+        for g, v in big.items():
+            lines.append(f"#define MR_BND_Q{l}_{g} {v * 1.0001:.5f}")
+
     # ---- beta quadratic forms, blocks by parity class ----
     def gram2(kappa, n):
         G = sp.zeros(n, n)

@@ -25,6 +25,7 @@ hipError_t mr_launch_stage1(hipStream_t, int, int, int, mr_inst*, const mr_tile1
 hipError_t mr_launch_fused1(hipStream_t, int, int, int, mr_inst*, const mr_tile1*, int, int);
 hipError_t mr_launch_stage2(hipStream_t, int, int, int, int, mr_inst*, const mr_tile2*, int, int, int);
 hipError_t mr_launch_kxrcf2(hipStream_t, int, int, int, mr_inst*, const mr_tile2*, int, int);
+hipError_t mr_launch_kxrcf2_few(hipStream_t, int, int, mr_inst*, const mr_tile2*, int, int);
 hipError_t mr_launch_values(hipStream_t, int, int, int, mr_inst*, const mr_tile1*, int, double*);
 hipError_t mr_launch_fb_reset(hipStream_t, int*, int);
 hipError_t mr_launch_pack(hipStream_t, const void*, mr_learn_w*);
@@ -53,6 +54,7 @@ constexpr int kKxRows = 46; /* ... x up to 46 flag rows of the extended flag ran
 constexpr int kKxMinRows = 8;
 constexpr int kKxMaxRows = 256; /* tallest height a caller may set */
 constexpr int kKxFill = 512; /* work groups that fill the GPU (256 CUs x 2 resident)    */
+constexpr int kKxFew = 1024; /* strips of k2_kxrcf_few that give every SIMD one wave    */
 constexpr int kLearnW = 64;     /* learned-indicator work item: 64 columns ...       */
 constexpr int kLearnRows = 160; /* ... x at most 160 rows of the extended flag range  */
 constexpr int kLearnFill = 512; /* work groups of it that fill the GPU               */
@@ -175,6 +177,27 @@ int kx_tiles(const mrhweno_problem& p, int rows = 0) {
              : 0;
 }
 
+/* Height of the strips of a KXRCF launch over the problems ps that gives
+   every strip one wave (k2_kxrcf_few), 0 if k2_kxrcf serves it: the lowest
+   that leaves a SIMD one wave, as the launch then lasts as long as a strip
+   and each row adds 5 us to 11.  Component-wise 16 us at 96^2 where the
+   lowest strips of k2_kxrcf take 22; 23 and 24 at 331 x 257 (two rows), 29
+   and 33 at 400^2 (three); four rows (512 x 384) would take 35 and 32.
+   Characteristic-wise a row costs more: 61 and 72 us at 96^2, 101 and 78 at
+   331 x 257, so one row only. */
+int kx_few_rows(const std::vector<const mrhweno_problem*>& ps, bool ch) {
+  for (int r = 1; r <= (ch ? 1 : 3); ++r) {
+    long long n = 0;
+    for (auto* p : ps) n += kx_tiles(*p, r);
+    if (n <= kKxFew) return n > 0 ? r : 0;
+  }
+  return 0;
+}
+/* an upper bound of the KXRCF work items of one instance */
+size_t kx_bound(const mrhweno_problem& p) {
+  return kx_tiles(p) > 0 ? (size_t)kx_tiles(p, kKxMinRows) + std::min(kKxFew, kx_tiles(p, 1)) : 0;
+}
+
 std::string validate(const mrhweno_problem& p) {
   if (p.dim != 1 && p.dim != 2) return "dim must be 1 or 2";
   if (p.nx < 8 || (p.dim == 2 && p.ny < 8)) return "grid must have at least 8 cells per direction";
@@ -267,9 +290,9 @@ Layout layout(const mrhweno_problem* P, int n) {
     size_t a = ceil_div(plane_of(p), kBlock) + ceil_div((long long)sex(p) * sey(p), kBlock) +
                ceil_div((long long)fex(p) * fey(p), kBlock) + ceil_div(plane_of(p), kBlock);
     if (p.dim == 1) a += ceil_div(p.nx, kFused1);
-    else t2 += 2 * strip_bound(p) + kx_tiles(p, kKxMinRows);   /* 2: strips along a side with data are lower */
+    else t2 += 2 * strip_bound(p) + kx_bound(p);   /* 2: strips along a side with data are lower */
     t1 += a;
-    tmax = std::max(tmax, a + (learned(p) ? learn_bound(p) : 0) + kx_tiles(p) +
+    tmax = std::max(tmax, a + (learned(p) ? learn_bound(p) : 0) + kx_bound(p) +
                               (p.dim == 2 ? strip_bound(p) : 0));
     if (learned(p)) L.n_tilesl += learn_bound(p);
     if (learned(p)) L.n_band += (size_t)fex(p) * fey(p);
@@ -317,6 +340,7 @@ struct Group {
   std::vector<int> insts;
   int t_summ = 0, n_summ = 0, t_flag = 0, n_flag = 0, t_st1 = 0, n_st1 = 0;
   int t_st2 = 0, n_st2 = 0, t_kx = 0, n_kx = 0, t_tvb = 0, n_tvb = 0;
+  bool kx_few = false;   /* the KXRCF strips are those of k2_kxrcf_few */
 };
 
 /* KXRCF work items of one instance (instance id `slot`) */
@@ -376,7 +400,7 @@ struct mrhweno_ctx {
   std::vector<mr_tile1> h_t1;
   std::vector<mr_tile2> h_t2;
   int rows2 = 0, grid2 = 0;   /* 0: chosen per launch (strip_rows) */
-  int kx_rows2 = 0;   /* rows of a 2D KXRCF work item (0: chosen per problem) */
+  int kx_rows2 = 0;   /* rows of a 2D KXRCF work item (0: chosen by size) */
   int nxcd = 1;       /* XCDs of the device (work-list order) */
   /* learned indicator */
   bool any_learned = false, weights_set = false;
@@ -534,7 +558,12 @@ static void build_lists(mrhweno_ctx* c) {
     }
     g.n_st2 = (int)c->h_t2.size() - g.t_st2;
     g.t_kx = (int)c->h_t2.size();
-    for (int q : g.insts) add_kx_tiles_if(c->h_t2, q, c->probs[q], false, c->kx_rows2, c->nxcd);
+    std::vector<const mrhweno_problem*> ks;
+    for (int q : g.insts)
+      if (kx_tiles(c->probs[q]) > 0 && !tvb(c->probs[q])) ks.push_back(&c->probs[q]);
+    const int few = g.nc == 4 && g.gb == 0 && c->kx_rows2 == 0 ? kx_few_rows(ks, g.ch) : 0;
+    g.kx_few = few > 0;
+    for (int q : g.insts) add_kx_tiles_if(c->h_t2, q, c->probs[q], false, few > 0 ? few : c->kx_rows2, c->nxcd);
     g.n_kx = (int)c->h_t2.size() - g.t_kx;
     g.t_tvb = (int)c->h_t2.size();
     for (int q : g.insts) add_kx_tiles_if(c->h_t2, q, c->probs[q], true, c->kx_rows2, c->nxcd);
@@ -565,6 +594,14 @@ static hipError_t mark(mrhweno_ctx* c, mr_prof* P, int cls) {
   return hipEventRecord(P->ev[P->n++], c->stream);
 }
 
+/* the KXRCF pass over a group's strips */
+static hipError_t launch_kx(mrhweno_ctx* c, const Group& g, int st) {
+  const int nk = g.nc == 4 ? (g.ch ? 4 : 3) : 1;
+  const mr_tile2* t = c->t2 + g.t_kx;
+  return g.kx_few ? mr_launch_kxrcf2_few(c->stream, nk, g.bp, c->d, t, g.n_kx, st)
+                  : mr_launch_kxrcf2(c->stream, nk, g.bp, g.gb, c->d, t, g.n_kx, st);
+}
+
 /* the kernels of one SSP-RK3 step, in order; with P, an event is recorded
    after every kernel class (class ids: 0 reduce/dt, 1 summary, 2 flags,
    3 stage) */
@@ -590,9 +627,7 @@ static hipError_t enqueue_step(mrhweno_ctx* c, mr_prof* P = nullptr) {
     for (auto& g : c->groups) {
       if (g.n_kx > 0) {
         any = true;
-        if ((e = mr_launch_kxrcf2(s, g.nc == 4 ? (g.ch ? 4 : 3) : 1, g.bp, g.gb, c->d, c->t2 + g.t_kx, g.n_kx, st)) !=
-            hipSuccess)
-          return e;
+        if ((e = launch_kx(c, g, st)) != hipSuccess) return e;
       }
       if (g.n_tvb > 0) {   /* the TVB test reads the indicator variable only */
         any = true;
@@ -906,8 +941,7 @@ mrhweno_status mrhweno_autotune_indicator(mrhweno_ctx* c, const int* rows_cand, 
     auto launch = [&]() -> hipError_t {
       for (auto& g : c->groups)
         if (g.n_kx > 0) {
-          hipError_t e = mr_launch_kxrcf2(c->stream, g.nc == 4 ? (g.ch ? 4 : 3) : 1, g.bp, g.gb, c->d, c->t2 + g.t_kx,
-                                          g.n_kx, 3);
+          hipError_t e = launch_kx(c, g, 3);
           if (e != hipSuccess) return e;
         }
       return hipSuccess;
@@ -1015,10 +1049,10 @@ struct ProbeLists {
   std::vector<mr_tile1> t1;
   std::vector<mr_tile2> t2, t3;
   int n_red = 0, t_sum = 0, n_sum = 0, t_flg = 0, n_flg = 0, t_val = 0, n_val = 0, t_st = 0, n_st = 0;
-  bool kx2 = false;
+  bool kx2 = false, kx_few = false;
 };
 
-static ProbeLists probe_lists(const mrhweno_problem& p, int slot) {
+static ProbeLists probe_lists(const mrhweno_problem& p, const mr_inst& I, int slot) {
   ProbeLists L;
   const bool lrn = learned(p);
   add_cells(L.t1, slot, plane_of(p));
@@ -1043,7 +1077,11 @@ static ProbeLists probe_lists(const mrhweno_problem& p, int slot) {
   }
   L.n_st = (int)L.t1.size() - L.t_st;
   if (lrn) add_learn_tiles(L.t3, slot, p, learn_rows({&p}));
-  if (L.kx2) add_kx_tiles(L.t3, slot, p);
+  if (L.kx2) {
+    const int few = ncomp_of(p) == 4 && !tvb(p) && gb_of(I) == 0 ? kx_few_rows({&p}, p.charwise) : 0;
+    L.kx_few = few > 0;
+    add_kx_tiles(L.t3, slot, p, few);
+  }
   return L;
 }
 
@@ -1071,9 +1109,12 @@ static hipError_t probe_kernels(hipStream_t s, const mrhweno_problem& p, const m
   if ((e = mr_launch_summary(s, p.dim, p.beta_on, gb_of(I), d, t1 + L.t_sum, L.n_sum, 3)) != hipSuccess) return e;
   if ((e = mr_launch_flags(s, p.dim, d, t1 + L.t_flg, L.n_flg, 3)) != hipSuccess) return e;
   const int ch = p.dim == 2 && p.charwise;
-  if (L.kx2 && (e = mr_launch_kxrcf2(s, ncomp_of(p) == 4 && !tvb(p) ? (ch ? 4 : 3) : 1, p.beta_on, gb_of(I), d,
-                                     t3, (int)L.t3.size(), 3)) != hipSuccess)
-    return e;
+  if (L.kx2) {
+    const int nk = ncomp_of(p) == 4 && !tvb(p) ? (ch ? 4 : 3) : 1, nt = (int)L.t3.size();
+    e = L.kx_few ? mr_launch_kxrcf2_few(s, nk, p.beta_on, d, t3, nt, 3)
+                 : mr_launch_kxrcf2(s, nk, p.beta_on, gb_of(I), d, t3, nt, 3);
+    if (e != hipSuccess) return e;
+  }
   const int nc = ncomp_of(p);
   if (kind == 0 && (e = mr_launch_values(s, p.dim, nc, p.beta_on, d, t1 + L.t_val, L.n_val, (double*)out)) != hipSuccess)
     return e;
@@ -1113,7 +1154,7 @@ static mrhweno_status probe(mrhweno_ctx* c, int q, const void* U, void* out, voi
   double* al_buf = (double*)(c->ws + c->L.probe_aleph);
   I.aleph = aleph ? al_buf : nullptr;
   const int slot = c->n;
-  const ProbeLists PL = probe_lists(p, slot);
+  const ProbeLists PL = probe_lists(p, I, slot);
   /* the probe area holds the 1D list, the 2D list and the learned or the
      2D KXRCF list */
   char* area = c->ws + c->L.probe_tiles;
@@ -1205,7 +1246,9 @@ mrhweno_status mrhweno_residual_noalloc(const mrhweno_problem* pp, const void* U
   if ((reinterpret_cast<uintptr_t>(U) & 7) != 0 || (reinterpret_cast<uintptr_t>(R) & 7) != 0)
     return fail(nullptr, MRHWENO_ERR_INVALID_ARG, "state and residual must be 8-byte aligned");
   /* scratch layout: descriptor | lists | flag plane | 1D face summaries */
-  const ProbeLists PL = probe_lists(p, 0);
+  mr_inst I;
+  fill_inst(p, I);
+  const ProbeLists PL = probe_lists(p, I, 0);
   size_t o2 = 0, o3 = 0;
   const size_t o_lists = al(sizeof(mr_inst));
   const size_t o_fl = o_lists + al(probe_list_bytes(PL, &o2, &o3));
@@ -1218,8 +1261,6 @@ mrhweno_status mrhweno_residual_noalloc(const mrhweno_problem* pp, const void* U
   unsigned char* base = nullptr;
   hipError_t e = scratch_ptr(&base);
   if (e != hipSuccess) return fail(nullptr, MRHWENO_ERR_DEVICE, std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e));
-  mr_inst I;
-  fill_inst(p, I);
   I.buf[0] = (double*)U;
   I.p_in[0] = (const double*)U;
   I.p_un = (const double*)U;

@@ -194,6 +194,24 @@ MR_DEV inline void mr2_maps(const double u[9], const double v[9], const double w
   q4[20] = -MR_KT(78) * a20 + MR_KT(79) * c20 + MR_KT(80) * c22;
   /* 119 non-zero map entries after the parity split */
 }
+/* largest |coefficient| of a datum in q_l - u_5 at the face points (rounded up):
+   UE, UC: averages of the edge and corner neighbours minus u_5; M0, ME, MC:
+   first moments of the cell, its edge and its corner neighbours */
+#define MR_BND_Q2_UE 0.14001
+#define MR_BND_Q2_UC 0.26253
+#define MR_BND_Q2_M0 0.00000
+#define MR_BND_Q2_ME 0.00000
+#define MR_BND_Q2_MC 0.00000
+#define MR_BND_Q3_UE 0.08774
+#define MR_BND_Q3_UC 0.13751
+#define MR_BND_Q3_M0 5.45509
+#define MR_BND_Q3_ME 0.00000
+#define MR_BND_Q3_MC 0.00000
+#define MR_BND_Q4_UE 0.25742
+#define MR_BND_Q4_UC 0.34411
+#define MR_BND_Q4_M0 4.46341
+#define MR_BND_Q4_ME 0.58902
+#define MR_BND_Q4_MC 0.96215
 MR_DEV inline double mr2_beta_k2(const double c[6]) {
   double b = 0.0, part;
   { const double t = MR_KT(83) * c[3];
