@@ -55,6 +55,11 @@ constexpr int kKxMinRows = 8;
 constexpr int kKxMaxRows = 256; /* tallest height a caller may set */
 constexpr int kKxFill = 512; /* work groups that fill the GPU (256 CUs x 2 resident)    */
 constexpr int kKxFew = 1024; /* strips of k2_kxrcf_few that give every SIMD one wave    */
+/* A replayed graph follows the one before after 8 us or more on the GPU (14
+   where the host launches graphs slower than they run): steps of grids up to
+   kManyCells cells, 0.3 ms or shorter, are replayed kManySteps at a time. */
+constexpr int kManySteps = 8;
+constexpr long long kManyCells = 1 << 18;
 constexpr int kLearnW = 64;     /* learned-indicator work item: 64 columns ...       */
 constexpr int kLearnRows = 160; /* ... x at most 160 rows of the extended flag range  */
 constexpr int kLearnFill = 512; /* work groups of it that fill the GPU               */
@@ -385,6 +390,11 @@ void add_learn_tiles(std::vector<mr_tile2>& v, int slot, const mrhweno_problem& 
 
 }  // namespace
 
+struct StepGraph {
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
+};
+
 struct mrhweno_ctx {
   int n = 0;
   hipStream_t stream = nullptr;
@@ -410,8 +420,7 @@ struct mrhweno_ctx {
   mr_tile2* tl = nullptr;
   int n_tl = 0, grid_l = 512, grid_fb = 1024;
   int learned_bp = 0;   /* some learned instance takes beta on p_l */
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
+  StepGraph one, many;   /* one step, kManySteps steps */
   bool any_lf = false;
   std::string err;
 };
@@ -656,20 +665,36 @@ static hipError_t enqueue_step(mrhweno_ctx* c, mr_prof* P = nullptr) {
   return hipSuccess;
 }
 
-static mrhweno_status rebuild_graph(mrhweno_ctx* c) {
-  if (c->exec) { (void)hipGraphExecDestroy(c->exec); c->exec = nullptr; }
-  if (c->graph) { (void)hipGraphDestroy(c->graph); c->graph = nullptr; }
-  if (!c->stream) return MRHWENO_OK;   /* the legacy default stream cannot be captured */
-  if (c->any_learned && !c->weights_set) return MRHWENO_OK;   /* captured once weights are set */
+static void drop_graphs(mrhweno_ctx* c) {
+  for (auto* g : {&c->one, &c->many}) {
+    if (g->exec) (void)hipGraphExecDestroy(g->exec);
+    if (g->graph) (void)hipGraphDestroy(g->graph);
+    *g = StepGraph{};
+  }
+}
+/* nsteps steps as a graph */
+static mrhweno_status capture_steps(mrhweno_ctx* c, int nsteps, StepGraph* out) {
   MR_CHECK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-  hipError_t e = enqueue_step(c);
+  hipError_t e = hipSuccess;
+  for (int k = 0; k < nsteps && e == hipSuccess; ++k) e = enqueue_step(c);
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(c->stream, &g);
+  if (e == hipSuccess && e2 == hipSuccess) out->graph = g;
+  else if (g) (void)hipGraphDestroy(g);
   if (e != hipSuccess) return fail(c, MRHWENO_ERR_DEVICE, std::string("capture: ") + hipGetErrorString(e));
   if (e2 != hipSuccess) return fail(c, MRHWENO_ERR_DEVICE, std::string("end capture: ") + hipGetErrorString(e2));
-  c->graph = g;
-  MR_CHECK(c, hipGraphInstantiate(&c->exec, c->graph, nullptr, nullptr, 0));
+  MR_CHECK(c, hipGraphInstantiate(&out->exec, out->graph, nullptr, nullptr, 0));
   return MRHWENO_OK;
+}
+static mrhweno_status rebuild_graph(mrhweno_ctx* c) {
+  drop_graphs(c);
+  if (!c->stream) return MRHWENO_OK;   /* the legacy default stream cannot be captured */
+  if (c->any_learned && !c->weights_set) return MRHWENO_OK;   /* captured once weights are set */
+  mrhweno_status st = capture_steps(c, 1, &c->one);
+  long long cells = 0;
+  for (auto& p : c->probs) cells += plane_of(p);
+  if (st == MRHWENO_OK && cells <= kManyCells) st = capture_steps(c, kManySteps, &c->many);
+  return st;
 }
 
 extern "C" {
@@ -810,8 +835,10 @@ mrhweno_status mrhweno_step(mrhweno_ctx* c, int nsteps) {
   if (nsteps < 0) return fail(c, MRHWENO_ERR_INVALID_ARG, "nsteps < 0");
   if (c->any_learned && !c->weights_set)
     return fail(c, MRHWENO_ERR_NOT_READY, "learned indicator has no weights (mrhweno_set_indicator)");
-  for (int k = 0; k < nsteps; ++k) {
-    if (c->exec) MR_CHECK(c, hipGraphLaunch(c->exec, c->stream));
+  int k = 0;
+  for (; c->many.exec && k + kManySteps <= nsteps; k += kManySteps) MR_CHECK(c, hipGraphLaunch(c->many.exec, c->stream));
+  for (; k < nsteps; ++k) {
+    if (c->one.exec) MR_CHECK(c, hipGraphLaunch(c->one.exec, c->stream));
     else MR_CHECK(c, enqueue_step(c));
   }
   return MRHWENO_OK;
@@ -1382,8 +1409,7 @@ const char* mrhweno_last_error(const mrhweno_ctx* c) {
 
 void mrhweno_destroy(mrhweno_ctx* c) {
   if (!c) return;
-  if (c->exec) (void)hipGraphExecDestroy(c->exec);
-  if (c->graph) (void)hipGraphDestroy(c->graph);
+  drop_graphs(c);
   delete c;
 }
 
