@@ -4,7 +4,7 @@
  *   k_reduce(0)  -> k_finalize                      (dt from U^n, CFL)
  *   per stage s = 0, 1, 2:
  *     [k_reduce(s) for Lax-Friedrichs alpha when s > 0]
- *     1D: k1_fused(s)                               (Step 2.1 and the stage in
+ *     1D: k1_fused(s) or k1_comp(s)                 (Step 2.1 and the stage in
  *                                                    one pass)
  *     2D: k2_kxrcf (Step 2.1, KXRCF) -> k2_stage(s) (Steps 1, 2.2, 2.3, fluxes,
  *                                                    residual, RK combination)
@@ -491,6 +491,138 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k1_fused(const mr_inst* __res
   }
 }
 
+/* k1_fused for the 1D Euler equations with the component-wise Step 1: wave c
+ * of a work group takes component c of its 64 cells (58 owned and three ring
+ * cells each side), so that the three Step 1 run side by side.  Every wave
+ * decides the flags by itself from the density's and momentum's values in
+ * LDS, and reconstructs its component again only where one of its cells is
+ * flagged; then wave 0 forms the numerical fluxes and wave 1 the quadrature
+ * of the physical one, and each wave updates its component.  Same
+ * arithmetic as k1_fused.
+ * What bounds it: one group's chain of loads, two Step 1 and the fluxes
+ * (five Step 1 in k1_fused, one after the other): 12.4 -> 7.3 us a stage at
+ * N = 4096; 15.8 -> 13.9 us over 24 instances of up to 16384 cells. */
+#define MR_C1 (64 - 6)   /* owned cells */
+template <bool BP, bool GB>
+__global__ __launch_bounds__(192) MR_OCC void k1_comp(const mr_inst* __restrict__ insts, const mr_tile1* __restrict__ tiles, int ntiles, int mode) {
+  mr_kt_fill();
+  __shared__ double s_v[3][4][64];    /* Step 1 of the stage input             */
+  __shared__ double s_w[3][4][64];    /* the same after the modification       */
+  __shared__ double s_fl[3][64];      /* numerical flux at the cell's left face */
+  __shared__ double s_F[3][64];       /* quadrature of the physical flux       */
+  const int cs = threadIdx.x % 64, c = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const mr_tile1 tl = tiles[t];
+    const mr_inst& I = insts[tl.inst];
+    if (!I.active) continue;
+    const int x = tl.start - 3 + cs;
+    const double tb = mr_stage_time(I, mode);
+    const mr_grid g{mr_gp(I.p_in[mode]), I.plane, I.nx, 1, I.bcx, I.bcy, 2, GB ? &I : nullptr, tb};
+    const mr_grid gn{mr_gp(I.p_un), I.plane, I.nx, 1, I.bcx, I.bcy, 2, GB ? &I : nullptr, mr_stage_time(I, 0)};
+    const bool kx = I.tc == 1 || I.tc == 4;
+    const bool out = cs >= 3 && x < tl.start + tl.count && x < I.nx;
+    /* averages and first moments of x - 2 .. x + 2 */
+    double u[5], v[5];
+    if (x >= 2 && x < I.nx - 2) {
+      const MR_GLB double* a = g.U + (long long)(2 * c) * I.plane + (x - 2);
+#pragma unroll
+      for (int k = 0; k < 5; ++k) { u[k] = a[k]; v[k] = a[I.plane + k]; }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) { u[k] = mr_ld(g, c, 0, x - 2 + k, 0); v[k] = mr_ld(g, c, 1, x - 2 + k, 0); }
+    }
+    double val[4];
+    if (kx) {
+      mr_recon1d<BP>(u[1], u[2], u[3], v[1], v[2], v[3], I.W, val);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s_v[c][q][cs] = val[q];
+    }
+    __syncthreads();
+    int f0 = I.tc == 2 ? 1 : 0;
+    if (kx && cs >= 1 && cs <= 62) {
+      const mr_grid gf{mr_gp(I.p_in[mode]), I.plane, I.nx, 1, I.bcx, I.bcy, 2, &I, tb};
+      double S[5], num, den, nrm = 0.0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) nrm = fmax(nrm, fabs(s_v[0][q][cs]));
+      S[0] = s_v[0][0][cs]; S[1] = s_v[0][3][cs]; S[4] = nrm;
+      const double l1 = s_v[0][3][cs - 1], r0 = s_v[0][0][cs + 1];
+      double l3 = l1, r2 = r0;
+      S[2] = S[0]; S[3] = S[1];
+      if (I.tc != 4) {
+        S[2] = s_v[1][0][cs] / S[0]; S[3] = s_v[1][3][cs] / S[1];
+        l3 = s_v[1][3][cs - 1] / l1; r2 = s_v[1][0][cs + 1] / r0;
+      }
+      f0 = mr1_flag(I, gf, x, tb, l1, l3, S, r0, r2, &num, &den) ? 1 : 0;
+    }
+    if (c == 0 && out) mr_gp(I.flags[mode == 0 ? 0 : 1])[x + I.fhalo] = (unsigned char)f0;
+    int fm = __shfl_up(f0, 1), fp = __shfl_down(f0, 1);
+    if (cs < 1 || cs > 62) f0 = 0;
+    const double v0s = v[2];   /* stored first moment */
+    if (f0) {
+      /* Steps 2.2/2.3: Step 1 again with the troubled cells' first moments modified */
+      const double vm = fm ? mr_modified_moment(u[0], u[2], v[0], v[2]) : v[1];
+      const double vp = fp ? mr_modified_moment(u[2], u[4], v[2], v[4]) : v[3];
+      v[2] = mr_modified_moment(u[1], u[3], v[1], v[3]);
+      v[1] = vm;
+      v[3] = vp;
+    }
+    if (!kx || __ballot(f0)) mr_recon1d<BP>(u[1], u[2], u[3], v[1], v[2], v[3], I.W, val);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s_w[c][q][cs] = val[q];
+    /* U^n with the stage-1 modification (stored first moments unless it persists) */
+    double un0 = 0.0, un1 = 0.0;
+    if (mode > 0 && out) {
+      const int f1 = I.mod == 0 ? mr_flag(mr_gp(I.flags[0]), I.fex, 1, I.fhalo, x, 0) : 0;
+      un0 = mr_ld(gn, c, 0, x, 0);
+      un1 = f1 ? mr_modified_moment(mr_ld(gn, c, 0, x - 1, 0), mr_ld(gn, c, 0, x + 1, 0), mr_ld(gn, c, 1, x - 1, 0),
+                                    mr_ld(gn, c, 1, x + 1, 0))
+               : mr_ld(gn, c, 1, x, 0);
+    }
+    __syncthreads();
+    if (c == 0 && cs >= 1) {
+      double a[3], b[3], f[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) { a[k] = s_w[k][3][cs - 1]; b[k] = s_w[k][0][cs]; }
+      mr_numflux<3, 0>(a, b, I.gam, 0.0, f);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) s_fl[k][cs] = f[k];
+    }
+    if (c == 1) {
+      double F[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        double pt[3], f[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) pt[k] = s_w[k][q][cs];
+        mr_physflux<3, 0>(pt, I.gam, f);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) F[k] += glw(q) * f[k];
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) s_F[k][cs] = F[k];
+    }
+    __syncthreads();
+    if (out) {
+      MR_GLB double* O = mr_gp(I.p_out[mode]);
+      const double dt = I.dt;
+      const double vt0 = u[2], vt1 = I.mod == 1 ? v0s : v[2];
+      const double fl = s_fl[c][cs], fr = s_fl[c][cs + 1];
+      const double L0 = -(fr - fl) / I.dx;
+      const double L1 = -(fr + fl) / (2.0 * I.dx) + s_F[c][cs] / I.dx;
+      double r0, r1;
+      if (mode == 0) { r0 = vt0 + dt * L0; r1 = vt1 + dt * L1; }
+      else {
+        const double a = mode == 1 ? 0.75 : 1.0 / 3.0, b = mode == 1 ? 0.25 : 2.0 / 3.0;
+        r0 = a * un0 + b * vt0 + b * dt * L0;
+        r1 = a * un1 + b * vt1 + b * dt * L1;
+      }
+      O[(long long)(c * 2 + 0) * I.plane + x] = r0;
+      O[(long long)(c * 2 + 1) * I.plane + x] = r1;
+    }
+    __syncthreads();
+  }
+}
+
 /* 1D final Gauss-Lobatto values of interior cells: gl[(c*4 + k)*nx + i]. */
 template <int NC, bool BP>
 __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k1_values(const mr_inst* __restrict__ insts, const mr_tile1* __restrict__ tiles, int ntiles, double* gl) {
@@ -619,11 +751,22 @@ hipError_t mr_launch_stage1(hipStream_t s, int nc, int bp, int gb, mr_inst* d, c
   return hipGetLastError();
 }
 
-/* the step's 1D stage with Step 2.1 (k1_fused), modes 0..2; tiles of at
+/* the step's 1D stage with Step 2.1 (k1_comp if comp, tiles of at most
+   MR_C1 cells; else k1_fused), modes 0..2; tiles of at
    most MR_BLOCK - 6 cells */
-hipError_t mr_launch_fused1(hipStream_t s, int nc, int bp, int gb, mr_inst* d, const mr_tile1* t, int nt, int mode) {
+hipError_t mr_launch_fused1(hipStream_t s, int nc, int bp, int gb, int comp, mr_inst* d, const mr_tile1* t, int nt,
+                            int mode) {
   if (nt <= 0) return hipSuccess;
   if (mode < 0 || mode > 2) return hipErrorInvalidValue;
+  if (comp) {
+    const dim3 G(nt), B(192);
+    if (nc != 3) return hipErrorInvalidValue;
+    if (bp && gb) hipLaunchKernelGGL((k1_comp<true, true>), G, B, 0, s, d, t, nt, mode);
+    else if (bp) hipLaunchKernelGGL((k1_comp<true, false>), G, B, 0, s, d, t, nt, mode);
+    else if (gb) hipLaunchKernelGGL((k1_comp<false, true>), G, B, 0, s, d, t, nt, mode);
+    else hipLaunchKernelGGL((k1_comp<false, false>), G, B, 0, s, d, t, nt, mode);
+    return hipGetLastError();
+  }
   const dim3 G(nt), B(MR_BLOCK);
 #define MR_LF(NC_, BP_)                                                                  \
   do {                                                                                   \
