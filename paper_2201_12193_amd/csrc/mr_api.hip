@@ -752,7 +752,7 @@ mrhweno_status mrhweno_create(const mrhweno_problem* probs, int n, void* const* 
     I.summ = needs_summ(p) ? (double*)(c->ws + c->L.summ[q]) : nullptr;
     I.aleph = nullptr;
     I.cur = 0;
-    if (p.flux == MRHWENO_BURGERS_LF) c->any_lf = true;
+    if (p.flux == MRHWENO_BURGERS_LF && p.dim == 2) c->any_lf = true;   /* 1D: k1_fused forms alpha */
   }
   std::memset(&c->h[n], 0, sizeof(mr_inst));
   {

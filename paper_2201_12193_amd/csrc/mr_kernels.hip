@@ -3,7 +3,7 @@
  * One SSP-RK3 step (eq. Runge-Kutta) is the launch sequence
  *   k_reduce(0)  -> k_finalize                      (dt from U^n, CFL)
  *   per stage s = 0, 1, 2:
- *     [k_reduce(s) for Lax-Friedrichs alpha when s > 0]
+ *     [k_reduce(s) for the 2D Lax-Friedrichs alpha when s > 0]
  *     1D: k1_fused(s) or k1_comp(s)                 (Step 2.1 and the stage in
  *                                                    one pass)
  *     2D: k2_kxrcf (Step 2.1, KXRCF) -> k2_stage(s) (Steps 1, 2.2, 2.3, fluxes,
@@ -369,6 +369,7 @@ MR_INL void mr1_stage_cell(const mr_inst& I, int mode, int x, bool out, int f0, 
     for (int c = 0; c < NC; ++c) s_fl[cs * NC + c] = fh_[c];
   }
   __syncthreads();
+  double ua = 0.0;
   if (out) {
     double F[NC];
 #pragma unroll
@@ -407,7 +408,15 @@ MR_INL void mr1_stage_cell(const mr_inst& I, int mode, int x, bool out, int f0, 
       }
       O[(long long)(c * 2 + 0) * P + x] = r0;
       O[(long long)(c * 2 + 1) * P + x] = r1;
+      if (NC == 1) ua = fabs(r0);
     }
+  }
+  if (NC == 1 && mode < 2) {
+    /* Lax-Friedrichs: the next stage's alpha is max |u| of this result, as
+       k_reduce would form it (a launch of 3 us more a stage) */
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ua = fmax(ua, __shfl_xor(ua, o));
+    if (cs % 64 == 0) atomicMax(const_cast<unsigned long long*>(&I.lfa[mode + 1]), mr_dbits(ua));
   }
 }
 
