@@ -26,7 +26,7 @@ hipError_t mr_launch_fused1(hipStream_t, int, int, int, int, mr_inst*, const mr_
 hipError_t mr_launch_stage2(hipStream_t, int, int, int, int, mr_inst*, const mr_tile2*, int, int, int);
 hipError_t mr_launch_kxrcf2(hipStream_t, int, int, int, mr_inst*, const mr_tile2*, int, int);
 hipError_t mr_launch_kxrcf2_few(hipStream_t, int, int, mr_inst*, const mr_tile2*, int, int);
-hipError_t mr_launch_values(hipStream_t, int, int, int, mr_inst*, const mr_tile1*, int, double*);
+hipError_t mr_launch_values(hipStream_t, int, int, int, int, mr_inst*, const mr_tile1*, int, double*);
 hipError_t mr_launch_fb_reset(hipStream_t, int*, int);
 hipError_t mr_launch_pack(hipStream_t, const void*, mr_learn_w*);
 hipError_t mr_launch_learned(hipStream_t, mr_inst*, const mr_tile2*, int, int, const mr_learn_w*, mr_band*, int*, int);
@@ -58,9 +58,9 @@ constexpr int kKxFill = 512; /* work groups that fill the GPU (256 CUs x 2 resid
 constexpr int kKxFew = 1024; /* strips of k2_kxrcf_few that give every SIMD one wave    */
 /* A replayed graph follows the one before after 8 us or more on the GPU (14
    where the host launches graphs slower than they run): steps of grids up to
-   kManyCells cells, 0.3 ms or shorter, are replayed kManySteps at a time. */
+   kManyCells cells, 0.2 ms or shorter, are replayed kManySteps at a time. */
 constexpr int kManySteps = 8;
-constexpr long long kManyCells = 1 << 18;
+constexpr long long kManyCells = 1 << 17;
 constexpr int kLearnW = 64;     /* learned-indicator work item: 64 columns ...       */
 constexpr int kLearnRows = 160; /* ... x at most 160 rows of the extended flag range  */
 constexpr int kLearnFill = 512; /* work groups of it that fill the GPU               */
@@ -1151,7 +1151,7 @@ static hipError_t probe_kernels(hipStream_t s, const mrhweno_problem& p, const m
     if (e != hipSuccess) return e;
   }
   const int nc = ncomp_of(p);
-  if (kind == 0 && (e = mr_launch_values(s, p.dim, nc, p.beta_on, d, t1 + L.t_val, L.n_val, (double*)out)) != hipSuccess)
+  if (kind == 0 && (e = mr_launch_values(s, p.dim, nc, p.beta_on, p.charwise, d, t1 + L.t_val, L.n_val, (double*)out)) != hipSuccess)
     return e;
   if (kind == 2) {
     if (p.dim == 1) e = mr_launch_stage1(s, nc, p.beta_on, gb_of(I), d, t1 + L.t_st, L.n_st, 3, 0);
@@ -1214,7 +1214,7 @@ static mrhweno_status probe(mrhweno_ctx* c, int q, const void* U, void* out, voi
       MR_CHECK(c, hipMemcpy2DAsync(out, p.nx, I.flags[0] + frow, I.fex, p.nx, p.ny, hipMemcpyDeviceToDevice, s));
     MR_CHECK(c, mr_launch_fallback(s, c->d, c->band, c->cnt, 3, c->grid_fb, p.beta_on));
     const int nc = ncomp_of(p);
-    if (kind == 0) MR_CHECK(c, mr_launch_values(s, p.dim, nc, p.beta_on, c->d, d1 + PL.t_val, PL.n_val, (double*)out));
+    if (kind == 0) MR_CHECK(c, mr_launch_values(s, p.dim, nc, p.beta_on, p.charwise, c->d, d1 + PL.t_val, PL.n_val, (double*)out));
     if (kind == 2) MR_CHECK(c, mr_launch_stage2(s, nc, p.beta_on, gb_of(I), 0, c->d, d2, (int)PL.t2.size(), 3, 0));
   } else {
     MR_CHECK(c, probe_kernels(s, p, I, c->d, slot, PL, d1, d2, d3, kind, out));

@@ -362,6 +362,18 @@ MR_INL int mr_flag(P fl, int ex, int ey, int h, int i, int j) {
  * stage input). */
 MR_INL void mr2_modify_stencil(const mr_grid& g, int c, int x, int y, const int* fs,
                                double* v, double* w) {
+  if (x >= 2 && x < g.nx - 2 && y >= 2 && y < g.ny - 2 && !(g.I && g.I->stepj > 0)) {
+    /* away from the edges the neighbours are at fixed offsets (mr2_stencil) */
+    const MR_GLB double* a = g.U + (long long)(c * 3) * g.P + (long long)y * g.nx + x;
+#pragma unroll
+    for (int l = 0; l < 9; ++l) {
+      if (!fs[l]) continue;
+      const MR_GLB double* q = a + (l / 3 - 1) * (long long)g.nx + (l % 3 - 1);
+      v[l] = mr_modified_moment(q[-1], q[1], q[g.P - 1], q[g.P + 1]);
+      w[l] = mr_modified_moment(q[-(long long)g.nx], q[g.nx], q[2 * g.P - g.nx], q[2 * g.P + g.nx]);
+    }
+    return;
+  }
 #pragma unroll
   for (int l = 0; l < 9; ++l) {
     if (!fs[l]) continue;

@@ -678,7 +678,14 @@ __global__ __launch_bounds__(MR_BLOCK) void k2_flags(const mr_inst* __restrict__
   }
 }
 
-template <int NC, bool BP>
+/* 2D final Gauss-Lobatto values of interior cells: gl[(c*16 + p)*plane +
+ * cell], a thread a cell and component (blockIdx.y); CH: the
+ * characteristic-wise set of the x direction, whose components come
+ * together.  Bound by instruction issue (the ghost rules of a troubled
+ * cell's loads were most of it): 258 -> 138 us at 512 x 384 with a component
+ * a thread, the two variants apart and the troubled cells' neighbours read
+ * at fixed offsets away from the edges. */
+template <int NC, bool BP, bool CH>
 __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_values(const mr_inst* __restrict__ insts, const mr_tile1* __restrict__ tiles, int ntiles, double* gl) {
   mr_kt_fill();
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
@@ -688,15 +695,13 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_values(const mr_inst* __re
     if (e >= tl.start + tl.count) continue;
     const int x = e % I.nx, y = e / I.nx;
     const mr_grid g{mr_gp(I.p_in[0]), I.plane, I.nx, I.ny, I.bcx, I.bcy, 3, &I, mr_stage_time(I, 3)};
-    if (NC == 4 && I.charwise) {
-      /* characteristic-wise: the set of the x direction */
+    if constexpr (CH) {
       double val[4][16];
       mr2_cell_values_ch<BP, 0>(g, I, mr_gp(I.flags[0]), x, y, val);
       for (int c = 0; c < 4; ++c)
         for (int p = 0; p < 16; ++p) gl[(long long)(c * 16 + p) * I.plane + e] = val[c][p];
-      continue;
-    }
-    for (int c = 0; c < NC; ++c) {
+    } else {
+      const int c = blockIdx.y;
       double val[16], a, b, d;
       mr2_cell_values<BP>(g, I, mr_gp(I.flags[0]), c, x, y, val, &a, &b, &d);
       for (int p = 0; p < 16; ++p) gl[(long long)(c * 16 + p) * I.plane + e] = val[p];
@@ -789,15 +794,17 @@ hipError_t mr_launch_fused1(hipStream_t s, int nc, int bp, int gb, int comp, mr_
   return hipGetLastError();
 }
 
-hipError_t mr_launch_values(hipStream_t s, int dim, int nc, int bp, mr_inst* d, const mr_tile1* t, int nt, double* gl) {
+hipError_t mr_launch_values(hipStream_t s, int dim, int nc, int bp, int ch, mr_inst* d, const mr_tile1* t, int nt, double* gl) {
   if (nt <= 0) return hipSuccess;
   const dim3 G(nt), B(MR_BLOCK);
   if (dim == 1) {
     if (nc == 1) { if (bp) hipLaunchKernelGGL((k1_values<1, true>), G, B, 0, s, d, t, nt, gl); else hipLaunchKernelGGL((k1_values<1, false>), G, B, 0, s, d, t, nt, gl); }
     else { if (bp) hipLaunchKernelGGL((k1_values<3, true>), G, B, 0, s, d, t, nt, gl); else hipLaunchKernelGGL((k1_values<3, false>), G, B, 0, s, d, t, nt, gl); }
   } else {
-    if (nc == 1) { if (bp) hipLaunchKernelGGL((k2_values<1, true>), G, B, 0, s, d, t, nt, gl); else hipLaunchKernelGGL((k2_values<1, false>), G, B, 0, s, d, t, nt, gl); }
-    else { if (bp) hipLaunchKernelGGL((k2_values<4, true>), G, B, 0, s, d, t, nt, gl); else hipLaunchKernelGGL((k2_values<4, false>), G, B, 0, s, d, t, nt, gl); }
+    const dim3 GC(nt, nc);
+    if (nc == 1) { if (bp) hipLaunchKernelGGL((k2_values<1, true, false>), GC, B, 0, s, d, t, nt, gl); else hipLaunchKernelGGL((k2_values<1, false, false>), GC, B, 0, s, d, t, nt, gl); }
+    else if (!ch) { if (bp) hipLaunchKernelGGL((k2_values<4, true, false>), GC, B, 0, s, d, t, nt, gl); else hipLaunchKernelGGL((k2_values<4, false, false>), GC, B, 0, s, d, t, nt, gl); }
+    else { if (bp) hipLaunchKernelGGL((k2_values<4, true, true>), G, B, 0, s, d, t, nt, gl); else hipLaunchKernelGGL((k2_values<4, false, true>), G, B, 0, s, d, t, nt, gl); }
   }
   return hipGetLastError();
 }
