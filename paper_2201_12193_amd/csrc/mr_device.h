@@ -384,30 +384,35 @@ MR_HD void mr_hllc(const double* uL, const double* uR, double gam, double* f) {
   const double muK = left ? muL : muR, pK = left ? pL : pR, irK = left ? irL : irR;
   const double w = speed(gam * irK, pK);
   const double sK = left ? muK - w : muK + w;
+  const double hK = k[NC - 1] + pK;
   /* f_K itself: 0 <= sL on the left, sR < 0 on the right -- and where a
-     point value has no sound speed (its pressure is not positive): every
-     comparison is then false, f_R is taken, and the NaN speeds must not
-     reach it */
-  const bool phys = (0.0 <= sK) == left;
-  double fK[NC];
-  fK[0] = k[N];
-  fK[1] = k[1] * muK;
-  if (NC == 4) fK[2] = k[2] * muK;
-  fK[N] += pK;
-  fK[NC - 1] = muK * (k[NC - 1] + pK);
+     point value has no sound speed (its pressure or density is not
+     positive): every comparison is then false and f_R is taken, as it is:
+     its mass flux is finite where the density is zero or not a number, so
+     the star state's terms are left out, not multiplied by zero */
+  if ((0.0 <= sK) == left) {
+    f[0] = k[N];
+    f[1] = k[1] * muK;
+    if (NC == 4) f[2] = k[2] * muK;
+    f[N] += pK;
+    f[NC - 1] = muK * hK;
+    return;
+  }
   /* rho_K (s_K - mu_K) / (s_K - s*) and p_K / (rho_K (s_K - mu_K)) share one
      reciprocal */
-  const double s = phys ? 0.0 : sK, sm = phys ? 0.0 : ss;
-  const double rd = k[0] * (s - muK), den = s - sm;
-  const double inv = phys ? 0.0 : mr_rcp(den * rd);
+  const double rd = k[0] * (sK - muK), den = sK - ss;
+  const double inv = mr_rcp(den * rd);
   const double fac = rd * rd * inv;
   double us[NC];
   us[0] = fac;
-  us[N] = fac * sm;
+  us[N] = fac * ss;
   if (NC == 4) us[T] = fac * (k[T] * irK);
-  us[NC - 1] = fac * (k[NC - 1] * irK + (sm - muK) * (sm + pK * (den * inv)));
-#pragma unroll
-  for (int c = 0; c < NC; ++c) f[c] = fK[c] + s * (us[c] - k[c]);
+  us[NC - 1] = fac * (k[NC - 1] * irK + (ss - muK) * (ss + pK * (den * inv)));
+  /* f_K + s_K (u* - u_K) */
+  f[0] = k[N] + sK * (us[0] - k[0]);
+  f[N] = fma(k[N], muK, pK) + sK * (us[N] - k[N]);
+  if (NC == 4) f[T] = fma(k[T], muK, sK * (us[T] - k[T]));
+  f[NC - 1] = fma(muK, hK, sK * (us[NC - 1] - k[NC - 1]));
 }
 
 /* Burgers' f(u) = u^2/2 with global Lax-Friedrichs. */

@@ -1,0 +1,61 @@
+"""States with NaN, infinite or zero entries: the one-off residual leaves
+finite what the formulas leave finite (the oracle's pattern), with the same
+flags, and the finite values agree to the bar of the other parity tests."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2201_12193_amd import inputs as I
+from tests.parity_util import TOL, comp_scale
+
+pytestmark = pytest.mark.gpu
+
+
+def _base(prob, seed=7):
+    """Random averages around a moderate state, small random first moments."""
+    rng = np.random.default_rng(seed)
+    shp = prob.shape()[2:]
+    U = np.zeros(prob.shape())
+    r, p = rng.uniform(0.8, 1.2, (2,) + shp)
+    u, v = rng.uniform(-0.3, 0.3, (2,) + shp)
+    U[:, 0] = I.euler1d_cons(r, u, p, 1.4) if prob.dim == 1 else I.euler2d_cons(r, u, v, p, 1.4)
+    U[:, 1:] = 0.01 * rng.uniform(-1, 1, U[:, 1:].shape)
+    return U
+
+
+def _run(tag, prob, U, clean):
+    """GPU and oracle residual and flags, and the scale of the residual."""
+    import torch
+    from paper_2201_12193_amd.mrhweno import Solver
+    print(f"nonfinite: {tag}", flush=True)
+    Ut = torch.from_numpy(np.ascontiguousarray(U)).cuda()
+    s = Solver([prob], [Ut.clone()])
+    R, fl = s.residual(0, Ut)
+    s.close()
+    with np.errstate(all="ignore"):
+        Lref, flref = oracle.residual(prob, U)
+    scale = comp_scale(prob, clean) / oracle.dt(prob, clean)
+    return R.cpu().numpy(), fl.cpu().numpy(), Lref, flref, scale.reshape((-1,) + (1,) * (U.ndim - 1))
+
+
+def _check(R, Lref, scale):
+    fin = np.isfinite(Lref)
+    assert np.array_equal(np.isfinite(R), fin)
+    assert (np.abs(R - Lref)[fin] <= TOL * (scale + np.abs(Lref))[fin]).all()
+
+
+@pytest.mark.parametrize("bc", [I.PERIODIC, I.REFLECTIVE])
+@pytest.mark.parametrize("value", [np.nan, np.inf, 0.0])
+def test_mass_flux_where_the_density_is_undefined_1d(value, bc):
+    """The mass flux of a state whose density is NaN, infinite or zero is its
+    momentum: the density's residual stays finite."""
+    prob = I.Problem(dim=1, nx=30, bc_x=bc, tc_mode=I.TC_NONE)
+    clean = _base(prob)
+    U = clean.copy()
+    if value == 0.0:
+        U[0, :, 12:15] = 0.0   # zero at every point of the middle cell
+    else:
+        U[0, 0, 12] = value
+    R, fl, Lref, flref, scale = _run(f"mass flux 1d density={value} bc={bc}", prob, U, clean)
+    assert np.isfinite(Lref[0]).all() and not np.isfinite(Lref[1:]).all()
+    _check(R[:1], Lref[:1], scale[:1])
