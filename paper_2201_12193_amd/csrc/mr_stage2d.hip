@@ -68,17 +68,22 @@ struct mr2_lds {
   double fs[4 * FS];          /* left-face sums (weights w, w eta), bottom-face sums */
 };
 
-/* A operand of mr2_sum that puts weight w of the lane's row into output row i */
-MR_INL double mr2_wrow(int i, double w) { return (int)(threadIdx.x & 3) == i ? w : 0.0; }
-/* acc + the sum over the four lanes of a cell of b times the A operand's
-   weights: lane 16 i + cell receives output row i (a zero weight still
-   spreads a NaN over the cell's rows, never to another cell) */
-MR_INL double mr2_sum(double a, double b, double acc) {
+/* The sum over the four lanes of a cell of b times the A operand's weights
+   (a: the weight of the lane's row, lane 16 k + cell), the same in every lane
+   of the cell: an operand of equal rows, so that the sum of one component,
+   should it not be finite, stays in that component (weights that are zero in
+   the other rows would hand a NaN on to them). */
+MR_INL double mr2_sum(double a, double b) {
 #ifdef __HIP_DEVICE_COMPILE__
-  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, 0.0, 0, 0, 0);
 #else
-  return acc + a * b;
+  return a * b;
 #endif
+}
+/* component k of four values */
+MR_INL double mr2_pick(int k, const double v[4]) {
+  const double a = k == 1 ? v[1] : v[0], b = k == 3 ? v[3] : v[2];
+  return k < 2 ? a : b;
 }
 
 MR_INL int mr_mod3(int y) { return ((y % 3) + 3) % 3; }
@@ -168,13 +173,10 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
   const int gc = NC == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / CW);
   const int gcol = tid % CW, em = gcol >> 2, ecol = CW + (gcol & 3);
   const bool ext = gcol < 12;
-  /* quadrature weights of this lane's row as A operands (see mr2_sum) */
-  const double lw = glw(k), lwe = glw(k) * gln(k);
-  double aF[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) aF[c] = mr2_wrow(c, lw * MR_W0);
-  const double aX = (tid & 1) ? mr2_wrow(1, lwe) : mr2_wrow(0, lw);
-  const double aY = (tid & 1) ? mr2_wrow(3, lwe) : mr2_wrow(2, lw);
+  /* quadrature weights of this lane's row as A operands (see mr2_sum): the
+     volume sums, and in alternate output rows the face sums with weights w
+     and w eta */
+  const double aF = glw(k) * MR_W0, aS = (tid & 1) ? glw(k) * gln(k) : glw(k);
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const mr_tile2 tl = tiles[t];
     const mr_inst& I = insts[tl.inst];
@@ -393,10 +395,14 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
         __syncthreads();
         /* the x set's sums at once: four registers instead of sixteen held
            through the y set's Step 1 */
+        {
+          double sF[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          fF = mr2_sum(aF[c], F[0][c], fF);
-          fs4[c] = mr2_sum(aX, fx[0][c], 0.0);
+          for (int c = 0; c < 4; ++c) {
+            sF[c] = mr2_sum(aF, F[0][c]);
+            fs4[c] = mr2_sum(aS, fx[0][c]);
+          }
+          fF = mr2_pick(k, sF);
         }
         /* field k of the y set (the stencil rows are still in place) */
         {
@@ -480,14 +486,17 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
       /* the quadratures over the rows: lane k receives component k's volume
          sums; the face sums of all components go through LDS */
       if constexpr (NC == 4) {
+        double sF[4], sG[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          if (!CH) fF = mr2_sum(aF[c], F[0][c], fF);
-          fG = mr2_sum(aF[c], G[0][c], fG);
-          if (!CH) fs4[c] = mr2_sum(aX, fx[0][c], 0.0);
+          if (!CH) sF[c] = mr2_sum(aF, F[0][c]);
+          sG[c] = mr2_sum(aF, G[0][c]);
+          if (!CH) fs4[c] = mr2_sum(aS, fx[0][c]);
+          const double sy = mr2_sum(aS, gy[0][c]);
+          FSM(k, c, cs) = k < 2 ? fs4[c] : sy;   /* rows 0, 1: left face; 2, 3: bottom face */
         }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) FSM(k, c, cs) = mr2_sum(aY, gy[0][c], fs4[c]);
+        if (!CH) fF = mr2_pick(k, sF);
+        fG = mr2_pick(k, sG);
       } else {
         double q0 = 0.0, q1 = 0.0, q2 = 0.0, q3 = 0.0;
 #pragma unroll

@@ -59,3 +59,23 @@ def test_mass_flux_where_the_density_is_undefined_1d(value, bc):
     R, fl, Lref, flref, scale = _run(f"mass flux 1d density={value} bc={bc}", prob, U, clean)
     assert np.isfinite(Lref[0]).all() and not np.isfinite(Lref[1:]).all()
     _check(R[:1], Lref[:1], scale[:1])
+
+
+@pytest.mark.parametrize("case", ["kxrcf", "none", "all", "tvb", "beta_p", "reflective", "transmissive"])
+@pytest.mark.parametrize("comp,value", [(3, np.nan), (3, np.inf), (3, -np.finfo(float).max), (2, np.nan), (1, np.nan)])
+def test_component_of_a_cell_2d(comp, value, case):
+    """One average that is not finite: the components, cells and faces that do
+    not depend on it keep their values (the volume and face sums of the 2D
+    stage kernel run over all components of a cell together)."""
+    kw = {"none": dict(tc_mode=I.TC_NONE), "all": dict(tc_mode=I.TC_ALL), "tvb": dict(tc_mode=I.TC_TVB),
+          "beta_p": dict(beta_on=I.BETA_ON_P), "reflective": dict(bc_x=I.REFLECTIVE, bc_y=I.REFLECTIVE),
+          "transmissive": dict(bc_x=I.TRANSMISSIVE, bc_y=I.TRANSMISSIVE)}.get(case, {})
+    prob = I.Problem(dim=2, nx=24, ny=20, x1=1.2, **kw)
+    clean = _base(prob)
+    for at in ((0, 0), (9, 10)):
+        U = clean.copy()
+        U[(comp, 0) + at] = value
+        R, fl, Lref, flref, scale = _run(f"2d {case} component {comp} = {value} at {at}", prob, U, clean)
+        assert not np.isfinite(Lref).all() and np.isfinite(Lref[0]).any()
+        _check(R, Lref, scale)
+        assert np.array_equal(fl, flref)
