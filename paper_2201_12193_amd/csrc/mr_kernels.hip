@@ -408,7 +408,7 @@ MR_INL void mr1_stage_cell(const mr_inst& I, int mode, int x, bool out, int f0, 
       }
       O[(long long)(c * 2 + 0) * P + x] = r0;
       O[(long long)(c * 2 + 1) * P + x] = r1;
-      if (NC == 1) ua = fabs(r0);
+      if (NC == 1) ua = fmax(ua, fabs(r0));   /* (a NaN leaves it, as in k_reduce) */
     }
   }
   if (NC == 1 && mode < 2) {

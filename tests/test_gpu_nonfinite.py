@@ -79,3 +79,31 @@ def test_component_of_a_cell_2d(comp, value, case):
         assert not np.isfinite(Lref).all() and np.isfinite(Lref[0]).any()
         _check(R, Lref, scale)
         assert np.array_equal(fl, flref)
+
+
+@pytest.mark.parametrize("nx", [130, 700])
+def test_alpha_beside_a_block_of_nan_1d(nx):
+    """1D Burgers with NaN first moments over more than a wave's cells: the
+    Lax-Friedrichs alpha of stages 2 and 3 comes from the other cells, which
+    the step advances as the oracle does."""
+    import torch
+    from paper_2201_12193_amd.mrhweno import Solver
+    print(f"nonfinite: alpha nx={nx}", flush=True)
+    prob = I.Problem(dim=1, nx=nx, system=I.BURGERS, tc_mode=I.TC_NONE)
+    U = np.zeros(prob.shape())
+    U[0, 0] = 0.3 + np.sin(2 * np.pi * (np.arange(nx) + 0.5) / nx)
+    clean = U.copy()
+    U[0, 1, 40:128] = np.nan
+    Ut = torch.from_numpy(U.copy()).cuda()
+    s = Solver([prob], [Ut])
+    s.step(1)
+    dt = s.last_dt()[0]
+    s.sync(raise_on_error=False)
+    s.close()
+    with np.errstate(all="ignore"):
+        ref = oracle.rk3_step(prob, U, dt)
+    fin = np.isfinite(ref)
+    assert fin[0, 0, 5:30].all() and not fin[0, 0, 50:120].any()
+    got = Ut.cpu().numpy()
+    assert np.array_equal(np.isfinite(got), fin)
+    assert np.abs(got - ref)[fin].max() <= TOL * comp_scale(prob, clean)[0]
