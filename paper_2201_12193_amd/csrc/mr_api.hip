@@ -22,7 +22,7 @@ hipError_t mr_launch_finalize(hipStream_t, mr_inst*, int, int);
 hipError_t mr_launch_summary(hipStream_t, int, int, int, mr_inst*, const mr_tile1*, int, int);
 hipError_t mr_launch_flags(hipStream_t, int, mr_inst*, const mr_tile1*, int, int);
 hipError_t mr_launch_stage1(hipStream_t, int, int, int, mr_inst*, const mr_tile1*, int, int, int);
-hipError_t mr_launch_fused1(hipStream_t, int, int, int, int, mr_inst*, const mr_tile1*, int, int);
+hipError_t mr_launch_fused1(hipStream_t, int, int, int, int, int, mr_inst*, const mr_tile1*, int, int);
 hipError_t mr_launch_stage2(hipStream_t, int, int, int, int, mr_inst*, const mr_tile2*, int, int, int);
 hipError_t mr_launch_kxrcf2(hipStream_t, int, int, int, mr_inst*, const mr_tile2*, int, int);
 hipError_t mr_launch_kxrcf2_few(hipStream_t, int, int, mr_inst*, const mr_tile2*, int, int);
@@ -45,6 +45,12 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kFused1 = kBlock - 6;   /* cells of a tile of the step's 1D kernel (three ring cells each side) */
 constexpr int kComp1 = 64 - 6;        /* ... with a wave a component (comp1)                                   */
+/* 1D Burgers instances of at most this many tiles: the stage forms the next
+   one's alpha, one atomic a tile, instead of a reduction launch of at most
+   512.  A step of 1000 cells 25.4 us (30.7 with the launch), of 64,000
+   (256 tiles) 36.6 (42.8), of 262,144 (1049) 75.1 (79.8); of 2^19 108.6 (106.1),
+   of 2^22 587 (481): there the tiles' atomics on one address hold it up. */
+constexpr int kLfTiles = 1024;
 constexpr int kFHalo = 2;   /* flags: final values of cells -1..n need flags -2..n+1 */
 constexpr int kSHalo = 3;   /* summaries: flags of cells -2..n+1 need summaries -3..n+2 */
 constexpr int kMinRows = 8; /* smallest 2D strip height a caller may set              */
@@ -347,7 +353,8 @@ struct Group {
   int dim, nc, bp;
   int gb;           /* boundary-data kernel variant (gb_of) */
   int ch;           /* characteristic-wise Step 1 */
-  bool any_summ = false, any_lf = false;
+  bool any_summ = false;
+  bool lf = false;   /* 1D Burgers whose stages form the next one's alpha (kLfTiles) */
   std::vector<int> insts;
   int t_summ = 0, n_summ = 0, t_flag = 0, n_flag = 0, t_st1 = 0, n_st1 = 0;
   int t_st2 = 0, n_st2 = 0, t_kx = 0, n_kx = 0, t_tvb = 0, n_tvb = 0;
@@ -427,7 +434,7 @@ struct mrhweno_ctx {
   int n_tl = 0, grid_l = 512, grid_fb = 1024;
   int learned_bp = 0;   /* some learned instance takes beta on p_l */
   StepGraph one, many;   /* one step, kManySteps steps */
-  bool any_lf = false;
+  bool any_lf = false;   /* some alpha of stages 2 and 3 comes from k_reduce */
   std::string err;
 };
 
@@ -664,7 +671,7 @@ static hipError_t enqueue_step(mrhweno_ctx* c, mr_prof* P = nullptr) {
       return e;
     if ((e = mark(c, P, 2)) != hipSuccess) return e;
     for (auto& g : c->groups) {
-      if (g.dim == 1) e = mr_launch_fused1(s, g.nc, g.bp, g.gb, comp1(c->probs[g.insts[0]]), c->d, c->t1 + g.t_st1, g.n_st1, st);
+      if (g.dim == 1) e = mr_launch_fused1(s, g.nc, g.bp, g.gb, comp1(c->probs[g.insts[0]]), g.lf, c->d, c->t1 + g.t_st1, g.n_st1, st);
       else e = mr_launch_stage2(s, g.nc, g.bp, g.gb, g.ch, c->d, c->t2 + g.t_st2, g.n_st2, st, c->grid2);
       if (e != hipSuccess) return e;
     }
@@ -752,7 +759,6 @@ mrhweno_status mrhweno_create(const mrhweno_problem* probs, int n, void* const* 
     I.summ = needs_summ(p) ? (double*)(c->ws + c->L.summ[q]) : nullptr;
     I.aleph = nullptr;
     I.cur = 0;
-    if (p.flux == MRHWENO_BURGERS_LF && p.dim == 2) c->any_lf = true;   /* 1D: k1_fused forms alpha */
   }
   std::memset(&c->h[n], 0, sizeof(mr_inst));
   {
@@ -800,6 +806,12 @@ mrhweno_status mrhweno_create(const mrhweno_problem* probs, int n, void* const* 
     if (!gp) { c->groups.push_back(Group{p.dim, nc, p.beta_on, gb_of(c->h[q]), ch}); gp = &c->groups.back(); }
     gp->insts.push_back(q);
     gp->any_summ |= needs_summ(p);
+  }
+  for (auto& g : c->groups) {
+    if (g.nc != 1) continue;
+    g.lf = g.dim == 1;
+    for (int q : g.insts) g.lf = g.lf && ceil_div_i(probs[q].nx, kFused1) <= kLfTiles;
+    c->any_lf |= !g.lf;
   }
   build_lists(c);
   mrhweno_status st;

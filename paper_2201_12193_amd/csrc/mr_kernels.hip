@@ -329,10 +329,12 @@ __global__ __launch_bounds__(MR_BLOCK) void k1_flags(const mr_inst* __restrict__
 /* Steps 1, 2.2, 2.3, fluxes, residual and RK combination of the cell x of
  * thread cs (the threads of a work group hold consecutive cells; the cell
  * of thread cs - 1 supplies the left face value), given the flags f0, fm,
- * fp of x, x - 1, x + 1; cells with `out` write their result.  Contains the
- * work group's barriers: every thread calls it. */
+ * fp of x, x - 1, x + 1; cells with `out` write their result.  Returns |u|
+ * of the result of a Burgers cell that writes one (0 else, and for a NaN,
+ * which k_reduce passes over as well).  Contains the work group's barriers:
+ * every thread calls it. */
 template <int NC, bool BP, bool GB>
-MR_INL void mr1_stage_cell(const mr_inst& I, int mode, int x, bool out, int f0, int fm, int fp, double* s_tr,
+MR_INL double mr1_stage_cell(const mr_inst& I, int mode, int x, bool out, int f0, int fm, int fp, double* s_tr,
                            double* s_fl) {
   const int cs = threadIdx.x;
   const int st = mode == 3 ? 0 : mode;
@@ -408,16 +410,10 @@ MR_INL void mr1_stage_cell(const mr_inst& I, int mode, int x, bool out, int f0, 
       }
       O[(long long)(c * 2 + 0) * P + x] = r0;
       O[(long long)(c * 2 + 1) * P + x] = r1;
-      if (NC == 1) ua = fmax(ua, fabs(r0));   /* (a NaN leaves it, as in k_reduce) */
+      if (NC == 1) ua = fmax(ua, fabs(r0));
     }
   }
-  if (NC == 1 && mode < 2) {
-    /* Lax-Friedrichs: the next stage's alpha is max |u| of this result, as
-       k_reduce would form it (a launch of 3 us more a stage) */
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ua = fmax(ua, __shfl_xor(ua, o));
-    if (cs % 64 == 0) atomicMax(const_cast<unsigned long long*>(&I.lfa[mode + 1]), mr_dbits(ua));
-  }
+  return ua;
 }
 
 /* 1D stage: one thread per cell of a block-sized tile; the two edge threads
@@ -455,10 +451,18 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k1_stage(const mr_inst* __res
  * cells and of their neighbours that the modification reads -- then the
  * stage (mr1_stage_cell) with those flags.  The flags of the owned cells
  * also go to the flag plane: stages 2 and 3 read back those of stage 1 for
- * U^n.  Same arithmetic as the three separate kernels. */
-template <int NC, bool BP, bool GB>
-__global__ __launch_bounds__(MR_BLOCK) MR_OCC void k1_fused(const mr_inst* __restrict__ insts, const mr_tile1* __restrict__ tiles, int ntiles, int mode) {
+ * U^n.  Same arithmetic as the three separate kernels.
+ *
+ * LF (Burgers, modes 0 and 1): also the next stage's Lax-Friedrichs alpha,
+ * max |u| of this one's result as k_reduce would form it, one atomic a tile;
+ * lf is the descriptors once more, for writing (a store through insts would
+ * turn their scalar loads into vector ones: 240 registers for 165).  See
+ * kLfTiles for the sizes that use it. */
+template <int NC, bool BP, bool GB, bool LF>
+__global__ __launch_bounds__(MR_BLOCK) MR_OCC void k1_fused(const mr_inst* __restrict__ insts, const mr_tile1* __restrict__ tiles, int ntiles, int mode,
+                                                            mr_inst* __restrict__ lf) {
   mr_kt_fill();
+  __shared__ double s_ua[MR_BLOCK / 64];
   __shared__ double s_sd[5 * MR_BLOCK];
   __shared__ unsigned char s_flg[MR_BLOCK];
   __shared__ double s_tr[MR_BLOCK * NC];
@@ -495,8 +499,15 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k1_fused(const mr_inst* __res
     const bool inner = cs >= 1 && cs <= MR_BLOCK - 2;
     const int f0 = inner ? s_flg[cs] : 0;
     const int fm = inner && f0 ? s_flg[cs - 1] : 0, fp = inner && f0 ? s_flg[cs + 1] : 0;
-    mr1_stage_cell<NC, BP, GB>(I, mode, x, own_cell, f0, fm, fp, s_tr, s_fl);
+    double ua = mr1_stage_cell<NC, BP, GB>(I, mode, x, own_cell, f0, fm, fp, s_tr, s_fl);
+    if (LF) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) ua = fmax(ua, __shfl_xor(ua, o));
+      if (cs % 64 == 0) s_ua[cs / 64] = ua;
+    }
     __syncthreads();
+    if (LF && cs == 0)
+      atomicMax(&lf[tl.inst].lfa[mode + 1], mr_dbits(fmax(fmax(s_ua[0], s_ua[1]), fmax(s_ua[2], s_ua[3]))));
   }
 }
 
@@ -766,10 +777,10 @@ hipError_t mr_launch_stage1(hipStream_t s, int nc, int bp, int gb, mr_inst* d, c
 }
 
 /* the step's 1D stage with Step 2.1 (k1_comp if comp, tiles of at most
-   MR_C1 cells; else k1_fused), modes 0..2; tiles of at
-   most MR_BLOCK - 6 cells */
-hipError_t mr_launch_fused1(hipStream_t s, int nc, int bp, int gb, int comp, mr_inst* d, const mr_tile1* t, int nt,
-                            int mode) {
+   MR_C1 cells; else k1_fused, tiles of at most MR_BLOCK - 6 cells), modes
+   0..2; lf: Burgers stages form the next one's alpha */
+hipError_t mr_launch_fused1(hipStream_t s, int nc, int bp, int gb, int comp, int lf, mr_inst* d, const mr_tile1* t,
+                            int nt, int mode) {
   if (nt <= 0) return hipSuccess;
   if (mode < 0 || mode > 2) return hipErrorInvalidValue;
   if (comp) {
@@ -782,15 +793,16 @@ hipError_t mr_launch_fused1(hipStream_t s, int nc, int bp, int gb, int comp, mr_
     return hipGetLastError();
   }
   const dim3 G(nt), B(MR_BLOCK);
-#define MR_LF(NC_, BP_)                                                                  \
-  do {                                                                                   \
-    if (gb) hipLaunchKernelGGL((k1_fused<NC_, BP_, true>), G, B, 0, s, d, t, nt, mode);  \
-    else hipLaunchKernelGGL((k1_fused<NC_, BP_, false>), G, B, 0, s, d, t, nt, mode);    \
+#define MR_F1(NC_, BP_, LF_)                                                                        \
+  do {                                                                                              \
+    if (gb) hipLaunchKernelGGL((k1_fused<NC_, BP_, true, LF_>), G, B, 0, s, d, t, nt, mode, d);     \
+    else hipLaunchKernelGGL((k1_fused<NC_, BP_, false, LF_>), G, B, 0, s, d, t, nt, mode, d);       \
   } while (0)
-  if (nc == 1) { if (bp) MR_LF(1, true); else MR_LF(1, false); }
-  else if (nc == 3) { if (bp) MR_LF(3, true); else MR_LF(3, false); }
+  if (nc == 1 && lf && mode < 2) { if (bp) MR_F1(1, true, true); else MR_F1(1, false, true); }
+  else if (nc == 1) { if (bp) MR_F1(1, true, false); else MR_F1(1, false, false); }
+  else if (nc == 3) { if (bp) MR_F1(3, true, false); else MR_F1(3, false, false); }
   else return hipErrorInvalidValue;
-#undef MR_LF
+#undef MR_F1
   return hipGetLastError();
 }
 
