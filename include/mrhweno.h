@@ -273,19 +273,20 @@ mrhweno_status mrhweno_residual_noalloc(const mrhweno_problem* prob, const void*
                                         void* residual_dev, void* flags_dev, void* hip_stream);
 
 /* Rows per work item of the 2D stage kernel and grid size (0 = one work
- * group per work item) -- the launch shape the autotuner chooses.  Where
- * work items of that height would leave the GPU short of work (fewer than
- * 512 in a launch) the library takes lower ones; without this call it
- * chooses the height itself.  Results do not depend on it. */
+ * group per work item) -- the launch shape the autotuner chooses; rows_2d in
+ * [8, 4096], or 0 for the height the library chooses by the size of the
+ * launch (the default: 32 rows, or lower ones, down to one row, where these
+ * would leave the GPU short of work).  Results do not depend on it. */
 mrhweno_status mrhweno_set_launch(mrhweno_ctx* ctx, int rows_2d, int grid_2d);
 
 /* Autotuner: time the 2D stage kernel (in its residual-only mode, which
  * leaves the state untouched) on the instances' current states for every
  * candidate launch shape -- rows per work item in rows_cand (n_rows
- * entries, each in [8, 4096]) and grid sizes in grid_cand (n_grid entries,
- * 0 = one work group per work item) -- with `reps` timed launches each, and
- * apply the fastest.  best_rows/best_grid/best_ms (host, may be NULL)
- * receive the choice and its mean launch time.  Synchronises. */
+ * entries, each 0 -- the height chosen by size -- or in [8, 4096]) and grid
+ * sizes in grid_cand (n_grid entries, 0 = one work group per work item) --
+ * with `reps` timed launches each, and apply the fastest.
+ * best_rows/best_grid/best_ms (host, may be NULL) receive the choice and its
+ * mean launch time.  Synchronises. */
 mrhweno_status mrhweno_autotune(mrhweno_ctx* ctx, const int* rows_cand, int n_rows,
                                 const int* grid_cand, int n_grid, int reps,
                                 int* best_rows, int* best_grid, float* best_ms);

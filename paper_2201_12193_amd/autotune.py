@@ -15,15 +15,15 @@ from typing import NamedTuple, Optional
 
 CACHE = os.path.join(os.path.expanduser(os.environ.get("MRHWENO_CACHE_DIR", "~/.cache/mrhweno")),
                      "autotune.json")
-ROWS = (8, 16, 24, 32, 40, 48, 56, 64, 72, 96)
-KX_ROWS = (0, 8, 16, 24, 32, 46, 64, 96, 140)   # 0: the height chosen per problem
+ROWS = (0, 8, 16, 24, 32, 40, 48, 56, 64, 72, 96)
+KX_ROWS = (0, 8, 16, 24, 32, 46, 64, 96, 140)   # 0 in both: the height the library chooses by size
 
 
 class Launch(NamedTuple):
-    rows: int          # rows per work item of the 2D stage kernel
+    rows: int          # rows per work item of the 2D stage kernel (0: by size)
     grid: int          # its grid (0: one work group per work item)
     ms: Optional[float]
-    kx_rows: int       # flag rows per work item of the 2D KXRCF pass (0: per problem)
+    kx_rows: int       # flag rows per work item of the 2D KXRCF pass (0: by size)
 
 
 def _arch() -> str:

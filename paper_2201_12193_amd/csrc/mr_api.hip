@@ -138,9 +138,9 @@ long long strip_count(const mrhweno_problem& p, int rows) { return (long long)st
 size_t strip_bound(const mrhweno_problem& p) {
   return (size_t)(strip_count(p, kMinRows) + std::min<long long>(kFewStrips, strip_count(p, 1)));
 }
-/* Height of the 2D stage strips of a launch over the problems ps: `rows`
-   (0: none set, kDefRows) or less where strips of that height leave the GPU
-   short of work.  A strip of h rows takes h + 2 row steps, one after
+/* Height of the 2D stage strips of a launch over the problems ps: `rows` if
+   the caller set one, else kDefRows or less where strips of that height
+   leave the GPU short of work.  A strip of h rows takes h + 2 row steps, one after
    another, so on a small grid the launch lasts as long as one strip: with a
    work group to itself a CU does a row step in 4.35 us, two resident ones
    take 6.6 us a step (15 and 22 characteristic-wise, the same ratio), and a
@@ -149,19 +149,18 @@ size_t strip_bound(const mrhweno_problem& p) {
    96 x 96 cells 1 row, 23 us (32 rows: 157); 331 x 257 4 rows, 49 us (159);
    512 x 384 7 rows, 69 us (158); 1024 x 1024 24 rows, 257 us (318).  From
    2048 strips on the rounds overlap and the height matters little, so it
-   stays; so does a height the caller set that fills the GPU. */
+   stays. */
 int strip_rows(const std::vector<const mrhweno_problem*>& ps, int rows) {
-  const int top = rows > 0 ? rows : kDefRows;
+  if (rows > 0) return rows;
   auto count = [&](int h) {
     long long n = 0;
     for (auto* p : ps) n += strip_count(*p, h);
     return n;
   };
-  const long long n0 = count(top);
-  if (n0 >= 4 * 512 || (rows > 0 && n0 >= 512)) return top;
-  int best = top;
+  if (count(kDefRows) >= 4 * 512) return kDefRows;
+  int best = kDefRows;
   double bc = -1.0;
-  for (int h = top; h >= 1; --h) {
+  for (int h = kDefRows; h >= 1; --h) {
     const long long n = count(h), rem = n % 512;
     if (h < kMinRows && n > kFewStrips) break;   /* the lists are sized for no more */
     const double cost = (double)(n / 512) * (10.0 + 6.6 * (h + 2)) +
@@ -839,8 +838,8 @@ mrhweno_status mrhweno_create(const mrhweno_problem* probs, int n, void* const* 
 
 mrhweno_status mrhweno_set_launch(mrhweno_ctx* c, int rows_2d, int grid_2d) {
   if (!c) return fail(nullptr, MRHWENO_ERR_INVALID_ARG, "NULL context");
-  if (rows_2d < kMinRows || rows_2d > 4096 || grid_2d < 0)
-    return fail(c, MRHWENO_ERR_INVALID_ARG, "rows_2d must be in [8, 4096], grid_2d >= 0");
+  if ((rows_2d != 0 && rows_2d < kMinRows) || rows_2d > 4096 || grid_2d < 0)
+    return fail(c, MRHWENO_ERR_INVALID_ARG, "rows_2d must be 0 or in [8, 4096], grid_2d >= 0");
   MR_CHECK(c, hipStreamSynchronize(c->stream));
   c->rows2 = rows_2d;
   c->grid2 = grid_2d;
@@ -869,7 +868,8 @@ mrhweno_status mrhweno_autotune(mrhweno_ctx* c, const int* rows_cand, int n_rows
   if (!c || !rows_cand || n_rows <= 0 || reps <= 0 || (n_grid > 0 && !grid_cand))
     return fail(c, MRHWENO_ERR_INVALID_ARG, "bad autotune arguments");
   for (int a = 0; a < n_rows; ++a)
-    if (rows_cand[a] < kMinRows || rows_cand[a] > 4096) return fail(c, MRHWENO_ERR_INVALID_ARG, "rows candidate out of range");
+    if ((rows_cand[a] != 0 && rows_cand[a] < kMinRows) || rows_cand[a] > 4096)
+      return fail(c, MRHWENO_ERR_INVALID_ARG, "rows candidate out of range");
   mrhweno_status st = pull(c);
   if (st != MRHWENO_OK) return st;
   bool any2d = false;
@@ -938,7 +938,7 @@ mrhweno_status mrhweno_autotune(mrhweno_ctx* c, const int* rows_cand, int n_rows
   mrhweno_status s2 = upload_lists(c);
   if (st == MRHWENO_OK) st = s2;
   if (st == MRHWENO_OK) st = rebuild_graph(c);
-  if (best_rows) *best_rows = c->rows2 > 0 ? c->rows2 : kDefRows;
+  if (best_rows) *best_rows = c->rows2;
   if (best_grid) *best_grid = c->grid2;
   if (best_ms) *best_ms = best;
   return st;
