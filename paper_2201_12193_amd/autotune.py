@@ -3,15 +3,21 @@
 The C ABI's mrhweno_autotune times candidate 2D launch shapes of the stage
 kernel on the instances' current states (without advancing them) and applies
 the fastest; mrhweno_autotune_indicator does the same for the strip height of
-the 2D KXRCF pass.  This module remembers the choices per (GPU architecture,
-dimension, number of components, problem-size bucket) in a JSON file, so
-later contexts of the same kind apply them without re-timing."""
+the 2D KXRCF pass.  This module remembers the choices per GPU architecture,
+build of the library, kernel variants of the problems and problem-size bucket
+in a JSON file, so later contexts of the same kind apply them without
+re-timing."""
 from __future__ import annotations
 
+import functools
+import hashlib
 import json
 import math
 import os
 from typing import NamedTuple, Optional
+
+from . import inputs
+from . import mrhweno
 
 CACHE = os.path.join(os.path.expanduser(os.environ.get("MRHWENO_CACHE_DIR", "~/.cache/mrhweno")),
                      "autotune.json")
@@ -32,13 +38,28 @@ def _arch() -> str:
     return getattr(p, "gcnArchName", p.name).split(":")[0]
 
 
+@functools.lru_cache(maxsize=None)
+def _build(path: str) -> str:
+    """Hash of the built library: shapes timed with other kernels do not apply."""
+    with open(path, "rb") as f:
+        return hashlib.sha1(f.read()).hexdigest()[:12]
+
+
+def _variant(p) -> str:
+    """The kernels an instance takes: components, Step 1, smoothness
+    indicators, troubled-cell mode, data on the sides or a step."""
+    data = "d" if p.step_j > 0 or inputs.SIDES in (p.bc_x, p.bc_y) else ""
+    return f"nc{p.ncomp}{'c' if p.charwise else ''}{'p' if p.beta_on == inputs.BETA_ON_P else ''}t{p.tc_mode}{data}"
+
+
 def key(solver) -> str:
-    """arch / dim / ncomp / log2 bucket of the total 2D cell count"""
+    """arch / build / dim / variants of the 2D instances / log2 bucket of
+    their total cell count"""
     two = [p for p in solver.problems if p.dim == 2]
     cells = sum(p.ncell for p in two)
-    ncomp = max((p.ncomp for p in two), default=0)
     bucket = int(math.log2(max(cells, 1)))
-    return f"{_arch()}/dim2/nc{ncomp}/cells2^{bucket}"
+    variants = "+".join(sorted({_variant(p) for p in two}))
+    return f"{_arch()}/{_build(mrhweno.LIB_PATH)}/dim2/{variants}/cells2^{bucket}"
 
 
 def _load() -> dict:
