@@ -222,9 +222,13 @@ MR_INL double mr_ld(const mr_grid& g, int c, int m, int i, int j) {
 /* the 3 x 3 stencil of component c around (x, y): averages u, first moments
  * v, w (label order).  Away from the grid's edges (and the step) the loads
  * are one address and fixed row offsets; the ghost rules of mr_ld take about
- * twenty instructions a value, more than Step 1 takes on the whole stencil. */
+ * twenty instructions a value, more than Step 1 takes on the whole stencil.
+ * A wave with cells at an edge loads all of them by those rules, or it would
+ * run both paths (on 64 x 64 cells every wave has some: the characteristic-
+ * wise reconstruction took 775 to 830 us with both, 695 now). */
 MR_INL void mr2_stencil(const mr_grid& g, int c, int x, int y, double u[9], double v[9], double w[9]) {
-  if (x >= 1 && x < g.nx - 1 && y >= 1 && y < g.ny - 1 && !(g.I && g.I->stepj > 0)) {
+  const bool in = x >= 1 && x < g.nx - 1 && y >= 1 && y < g.ny - 1 && !(g.I && g.I->stepj > 0);
+  if (__ballot(!in) == 0ull) {
     const MR_GLB double* a = g.U + (long long)(c * 3) * g.P + (long long)(y - 1) * g.nx + (x - 1);
 #pragma unroll
     for (int l = 0; l < 9; ++l) {
@@ -362,7 +366,8 @@ MR_INL int mr_flag(P fl, int ex, int ey, int h, int i, int j) {
  * stage input). */
 MR_INL void mr2_modify_stencil(const mr_grid& g, int c, int x, int y, const int* fs,
                                double* v, double* w) {
-  if (x >= 2 && x < g.nx - 2 && y >= 2 && y < g.ny - 2 && !(g.I && g.I->stepj > 0)) {
+  const bool in = x >= 2 && x < g.nx - 2 && y >= 2 && y < g.ny - 2 && !(g.I && g.I->stepj > 0);
+  if (__ballot(!in) == 0ull) {
     /* away from the edges the neighbours are at fixed offsets (mr2_stencil) */
     const MR_GLB double* a = g.U + (long long)(c * 3) * g.P + (long long)y * g.nx + x;
 #pragma unroll
@@ -394,13 +399,11 @@ MR_INL void mr2_cell_values(const mr_grid& g, const mr_inst& I, const MR_GLB uns
                             int c, int x, int y, double out[16], double* ue, double* ve, double* we) {
   double u[9], v[9], w[9];
   int fs[9];
-  mr2_stencil(g, c, x, y, u, v, w);
-  fs[4] = mr_flag(fl, I.fex, I.fey, I.fhalo, x, y);
-  if (fs[4]) {
+  /* the flags in flight with the stencil: one latency, not three */
 #pragma unroll
-    for (int l = 0; l < 9; ++l) fs[l] = mr_flag(fl, I.fex, I.fey, I.fhalo, x + l % 3 - 1, y + l / 3 - 1);
-    mr2_modify_stencil(g, c, x, y, fs, v, w);
-  }
+  for (int l = 0; l < 9; ++l) fs[l] = mr_flag(fl, I.fex, I.fey, I.fhalo, x + l % 3 - 1, y + l / 3 - 1);
+  mr2_stencil(g, c, x, y, u, v, w);
+  if (fs[4]) mr2_modify_stencil(g, c, x, y, fs, v, w);
   *ue = u[4];
   *ve = v[4];
   *we = w[4];
