@@ -278,7 +278,7 @@ std::string validate(const mrhweno_problem& p) {
      of threads past the last cell) stay in 32 bits */
   if (p.dim == 1 && p.nx >= (1 << 30)) return "1D grid too large (at most 2^30 - 1 cells)";
   if (plane_of(p) > (1ll << 31) - 1) return "grid too large";
-  /* the 2D stage kernel addresses a moment plane and row as a 30-bit offset */
+  /* the KXRCF kernel addresses a row of up to twelve moment planes in 32 bits */
   if (p.dim == 2 && 13ll * plane_of(p) >= (1ll << 30)) return "2D grid too large (at most 2^30/13 cells)";
   return "";
 }

@@ -451,54 +451,6 @@ MR_INL void mr2_cell_values_ch(const mr_grid& g, const mr_inst& I, const MR_GLB 
   }
 }
 
-/* KXRCF face data of cell (i, j) from its Step-1 values, eqs. (KXRCF_),
- * (line-integral-average_): f[0..3] Gauss-Lobatto means of the indicator
- * variable (density; u for Burgers) on the left, right, bottom, top face,
- * f[4..7] the same for the normal velocity, f[8] the max |u| over the 16
- * points. */
-template <bool BP>
-MR_INL void mr2_face_summary(const mr_grid& g, const mr_inst& I, int i, int j, double f[9]) {
-  double irl[4], irr[4], irm[4];   /* 1/rho at points 0,4,8,12 | 3,7,11,15 | 1,2,13,14 */
-  double sl = 0.0, sr = 0.0, sb = 0.0, st = 0.0, nrm = 0.0;
-  double vl = 0.0, vr = 0.0, vb = 0.0, vt = 0.0;
-  const int ncomp = I.flux == 1 ? 3 : 1;
-#pragma unroll 1
-  for (int c = 0; c < ncomp; ++c) {
-    double u[9], v[9], w[9], r[16];
-    mr2_stencil(g, c, i, j, u, v, w);
-    mr_recon2d<BP>(u, v, w, I.W, r);
-    if (c == 0) {
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        sl += glw(m) * r[0 + 4 * m];
-        sr += glw(m) * r[3 + 4 * m];
-        sb += glw(m) * r[m];
-        st += glw(m) * r[12 + m];
-      }
-#pragma unroll
-      for (int k = 0; k < 16; ++k) nrm = fmax(nrm, fabs(r[k]));
-      if (ncomp == 1) { vl = sl; vr = sr; vb = sb; vt = st; }   /* Burgers: f'(u) = u */
-      else {
-        mr_recip4(r[0], r[4], r[8], r[12], irl);
-        mr_recip4(r[3], r[7], r[11], r[15], irr);
-        mr_recip4(r[1], r[2], r[13], r[14], irm);
-      }
-    } else if (c == 1) {
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        vl += glw(m) * (r[0 + 4 * m] * irl[m]);
-        vr += glw(m) * (r[3 + 4 * m] * irr[m]);
-      }
-    } else {
-      vb = glw(0) * (r[0] * irl[0]) + glw(1) * (r[1] * irm[0]) + glw(2) * (r[2] * irm[1]) + glw(3) * (r[3] * irr[0]);
-      vt = glw(0) * (r[12] * irl[3]) + glw(1) * (r[13] * irm[2]) + glw(2) * (r[14] * irm[3]) + glw(3) * (r[15] * irr[3]);
-    }
-  }
-  f[0] = sl; f[1] = sr; f[2] = sb; f[3] = st;
-  f[4] = vl; f[5] = vr; f[6] = vb; f[7] = vt;
-  f[8] = nrm;
-}
-
 template <int NC, int D>
 MR_INL void mr_numflux(const double* a, const double* b, double gam, double alpha, double* f) {
   if constexpr (NC == 1) f[0] = mr_lf(a[0], b[0], alpha);
@@ -559,30 +511,3 @@ MR_INL void mr_physflux(const double* u, double gam, double* f) {
   if constexpr (NC == 1) f[0] = 0.5 * u[0] * u[0];
   else mr_euler_flux<NC, D>(u, gam, f);
 }
-
-/* exchange with lane ^ 1 or lane ^ 2 inside a group of four lanes, through
- * the DPP quad permutation (no LDS traffic) */
-template <int X>
-MR_INL double mr_quad_xor(double v) {
-  constexpr int ctrl = X == 1 ? 0xB1 : 0x4E;   /* quad_perm [1,0,3,2] / [2,3,0,1] */
-  const long long b = __builtin_bit_cast(long long, v);
-  const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffll), ctrl, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), ctrl, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
-/* reduce-scatter over the NC lanes of a cell: lane k receives sum_r a_r[k] */
-template <int NC>
-MR_INL double mr_rs(const double (&a)[NC], int k) {
-  if (NC == 1) return a[0];
-  const bool hi = (k & 2) != 0;
-  const double s0 = hi ? a[0] : a[2], s1 = hi ? a[1] : a[3];
-  const double k0 = hi ? a[2] : a[0], k1 = hi ? a[3] : a[1];
-  const double b0 = k0 + mr_quad_xor<2>(s0);
-  const double b1 = k1 + mr_quad_xor<2>(s1);
-  const bool odd = (k & 1) != 0;
-  const double s = odd ? b0 : b1, kk = odd ? b1 : b0;
-  return kk + mr_quad_xor<1>(s);
-}
-
-/* 2D final Gauss-Lobatto values of interior cells: gl[(c*16 + p)*plane + cell]. */

@@ -395,7 +395,8 @@ __global__ __launch_bounds__(MR_BLOCK, 2) void k2_learned(const mr_inst* __restr
 /* KXRCF for the cells the network left undecided (band list, count
  * cnt[stage]) in one pass: fifteen threads per band cell reconstruct the
  * density and the momenta of the cell and of its four neighbours, five of
- * them form the face data (as mr2_face_summary), and the first evaluates eq.
+ * them form the face data (means and normal velocities on the four faces and
+ * the norm, eqs. (line-integral-average_)), and the first evaluates eq.
  * (KXRCF_) on it as the fused indicator kernel does.  The list is short
  * (thousands of cells), so the launch lasts as long as one group's chain of
  * loads and Step 1: 21 -> 13 us at 1024 x 1024 with the components on three
@@ -413,7 +414,7 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k_fb_direct(const mr_inst* __
   constexpr int PB = MR_BLOCK / 15;   /* band cells per block pass */
   __shared__ double pr[PB][5][12];    /* density at points 0,4,8,12 | 3,7,11,15 | 1,2,13,14 */
   __shared__ double pm[PB][5][2][8];  /* x momentum left | right, y momentum bottom | top   */
-  __shared__ double fs[PB][5][9];     /* face data (mr2_face_summary)                       */
+  __shared__ double fs[PB][5][9];     /* face averages, velocities, norm                     */
   const int n = cnt[stage];
   const int tid = threadIdx.x, cb = tid / 15, d = (tid % 15) / 3, c = tid % 3;
   for (int base = blockIdx.x * PB; base < n; base += gridDim.x * PB) {
