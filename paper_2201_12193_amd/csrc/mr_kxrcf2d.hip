@@ -1,7 +1,7 @@
 /* The fused 2D KXRCF / TVB indicator kernel (its own translation unit: it
  * keeps the constant table of the reconstruction in LDS, see mr_device.h). */
 #define MR_KT_IN_LDS 1
-#include "mr_common.h"
+#include "mr_kxrcf.h"
 
 /* ========================================= fused KXRCF / TVB (2D, tc = 1 or 4) */
 /* Troubled-cell flags of eq. (KXRCF_) with the face averages of eq.
@@ -16,17 +16,19 @@
  * in a ten-row LDS ring, each loaded from HBM once per work group with the
  * boundary condition applied: a step reads six rows and writes the four
  * that the next step adds.  The face data sit in a six-row ring. */
-#define KX_W 64                       /* reconstructed columns of a strip */
-#define KX_XW (KX_W + 2)              /* staged columns                   */
 #define KX_MR 10                      /* moment ring rows                 */
 #define KX_FR 6                       /* face data ring rows              */
 
 /* ring slot of row y >= -12 */
 MR_INL int kx_slot(int y, int n) { return (y + 12 * n) % n; }
 
-/* face data of the cell at staged column col whose rows y-1, y, y+1 sit in
-   ring slots s0, s1, s2 (f as mr2_face_summary; the velocities use shared
-   reciprocals of the density at the twelve face points) */
+/* KXRCF face data of a cell from its Step-1 values, eqs. (KXRCF_),
+   (line-integral-average_), the cell at staged column col whose rows y-1, y,
+   y+1 sit in ring slots s0, s1, s2: f[0..3] Gauss-Lobatto means of the
+   indicator variable (density; u for Burgers) on the left, right, bottom,
+   top face, f[4..7] the same for the normal velocity (with shared reciprocals
+   of the density at the twelve face points), f[8] the max |u| over the 16
+   points */
 template <int NK, bool BP>
 MR_INL void kx_face_data(const double (*mom)[3 * NK * KX_XW], int s0, int s1, int s2, int col,
                          const mr_wconst& W, double tvb_mh2, double f[9]) {
@@ -85,73 +87,6 @@ MR_INL void kx_face_data(const double (*mom)[3 * NK * KX_XW], int s0, int s1, in
   f[0] = sl; f[1] = sr; f[2] = sb; f[3] = st;
   f[4] = vl; f[5] = vr; f[6] = vb; f[7] = vt;
   f[8] = nrm;
-}
-
-/* face data of one direction D of the characteristic-wise Step 1 (2D
-   Euler, four components staged; see mr_char2): each field projected from
-   the stencil, reconstructed, and mapped back at the points the indicator
-   reads -- the density at all sixteen points (its norm), the density and
-   the normal momentum at the points of the two faces normal to D.
-   f[0..1] / f[4..5] (D = 0: left, right) or f[2..3] / f[6..7] (D = 1:
-   bottom, top) as kx_face_data; *nrm is raised to max |rho|. */
-template <bool BP, int D>
-MR_INL void kx_face_data_ch(const double (*mom)[3 * 4 * KX_XW], int s0, int s1, int s2, int col,
-                            const mr_wconst& W, double gam, double f[9], double* nrm) {
-  double u0[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) u0[c] = mom[s1][(3 * c + 0) * KX_XW + col];
-  const mr_char2 e = mr_char2_state<D>(u0, gam);
-  double rho[16], mn[8];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) rho[q] = 0.0;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) mn[q] = 0.0;
-#pragma unroll 1
-  for (int k = 0; k < 4; ++k) {
-    __asm__ volatile("" ::: "memory");   /* keep the constant table in LDS (see kx_face_data) */
-    double lk[4];
-    mr_char2_left<D>(e, k, lk);
-    double u[9], v[9], w[9], q[16];
-#pragma unroll
-    for (int l = 0; l < 9; ++l) {
-      const int dx = l % 3 - 1, slot = l < 3 ? s0 : (l < 6 ? s1 : s2);
-      u[l] = v[l] = w[l] = 0.0;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        u[l] += lk[c] * mom[slot][(3 * c + 0) * KX_XW + col + dx];
-        v[l] += lk[c] * mom[slot][(3 * c + 1) * KX_XW + col + dx];
-        w[l] += lk[c] * mom[slot][(3 * c + 2) * KX_XW + col + dx];
-      }
-    }
-    mr_recon2d<BP>(u, v, w, W, q);
-    /* column k of R: density entry 1, 1, 0, 1; normal momentum vn - c, vn, 0, vn + c */
-    const double rr = k == 2 ? 0.0 : 1.0;
-    const double rn = k == 0 ? e.vn - e.c : (k == 1 ? e.vn : (k == 2 ? 0.0 : e.vn + e.c));
-#pragma unroll
-    for (int p = 0; p < 16; ++p) rho[p] += rr * q[p];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int pa = D == 0 ? 4 * m : m, pb = D == 0 ? 3 + 4 * m : 12 + m;
-      mn[m] += rn * q[pa];
-      mn[4 + m] += rn * q[pb];
-    }
-  }
-#pragma unroll
-  for (int p = 0; p < 16; ++p) *nrm = fmax(*nrm, fabs(rho[p]));
-  double sa = 0.0, sb = 0.0, va = 0.0, vb = 0.0;
-  double ia[4], ib[4];
-  if (D == 0) { mr_recip4(rho[0], rho[4], rho[8], rho[12], ia); mr_recip4(rho[3], rho[7], rho[11], rho[15], ib); }
-  else { mr_recip4(rho[0], rho[1], rho[2], rho[3], ia); mr_recip4(rho[12], rho[13], rho[14], rho[15], ib); }
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int pa = D == 0 ? 4 * m : m, pb = D == 0 ? 3 + 4 * m : 12 + m;
-    sa += glw(m) * rho[pa];
-    sb += glw(m) * rho[pb];
-    va += glw(m) * (mn[m] * ia[m]);
-    vb += glw(m) * (mn[4 + m] * ib[m]);
-  }
-  f[2 * D] = sa; f[2 * D + 1] = sb;
-  f[4 + 2 * D] = va; f[5 + 2 * D] = vb;
 }
 
 /* NK: components the indicator reads (1 Burgers, 3 Euler: rho and the
@@ -248,9 +183,9 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_kxrcf(const mr_inst* __res
           /* characteristic-wise Step 1: x faces from the x set, y faces from the y set */
           f[8] = 0.0;
           kx_face_data_ch<BP, 0>(mom, kx_slot(r - 1, KX_MR), kx_slot(r, KX_MR), kx_slot(r + 1, KX_MR), cx + 1, I.W,
-                                 I.gam, f, &f[8]);
+                                 I.gam, f, &f[8], [] { __asm__ volatile("" ::: "memory"); });
           kx_face_data_ch<BP, 1>(mom, kx_slot(r - 1, KX_MR), kx_slot(r, KX_MR), kx_slot(r + 1, KX_MR), cx + 1, I.W,
-                                 I.gam, f, &f[8]);
+                                 I.gam, f, &f[8], [] { __asm__ volatile("" ::: "memory"); });
         } else {
           kx_face_data<NK, BP>(mom, kx_slot(r - 1, KX_MR), kx_slot(r, KX_MR), kx_slot(r + 1, KX_MR), cx + 1, I.W,
                                I.tc == 4 ? I.tvb_mh2 : -1.0, f);
