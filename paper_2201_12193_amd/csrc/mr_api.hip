@@ -595,6 +595,8 @@ static void build_lists(mrhweno_ctx* c) {
 }
 
 static mrhweno_status upload_lists(mrhweno_ctx* c) {
+  if (c->h_t1.size() > c->L.n_tiles1 || c->h_t2.size() > c->L.n_tiles2)
+    return fail(c, MRHWENO_ERR_DEVICE, "work lists exceed the workspace");
   MR_CHECK(c, hipMemcpy(c->t1, c->h_t1.data(), sizeof(mr_tile1) * std::max<size_t>(c->h_t1.size(), 1) , hipMemcpyHostToDevice));
   if (!c->h_t2.empty())
     MR_CHECK(c, hipMemcpy(c->t2, c->h_t2.data(), sizeof(mr_tile2) * c->h_t2.size(), hipMemcpyHostToDevice));
@@ -780,6 +782,10 @@ mrhweno_status mrhweno_create(const mrhweno_problem* probs, int n, void* const* 
     for (auto* p : ps) {
       add_learn_tiles(tl, (int)(p - probs), *p, learn_rows(ps));
       c->learned_bp |= p->beta_on;
+    }
+    if (tl.size() > c->L.n_tilesl) {
+      delete c;
+      return fail(nullptr, MRHWENO_ERR_DEVICE, "work lists exceed the workspace");
     }
     c->n_tl = (int)tl.size();
     int dev = 0, cus = 256;
