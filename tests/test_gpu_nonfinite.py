@@ -107,3 +107,23 @@ def test_alpha_beside_a_block_of_nan_1d(nx):
     got = Ut.cpu().numpy()
     assert np.array_equal(np.isfinite(got), fin)
     assert np.abs(got - ref)[fin].max() <= TOL * comp_scale(prob, clean)[0]
+
+
+@pytest.mark.parametrize("nx", [24, 70])
+@pytest.mark.parametrize("bc", [I.PERIODIC, I.REFLECTIVE, I.TRANSMISSIVE])
+@pytest.mark.parametrize("comp,value", [(0, np.nan), (0, np.inf), (0, 0.0), (0, -0.1), (1, np.inf), (2, np.nan),
+                                        (2, -np.inf), (1, 1e200), (0, 1e-300)])
+def test_flags_beside_a_state_that_is_not_physical_2d(comp, value, bc, nx):
+    """The KXRCF strips of small grids leave out the momenta's Step 1 where
+    bounds decide the velocities' signs: a value that is not finite, or no
+    positive density, takes the full path, and the flags are the oracle's."""
+    prob = I.Problem(dim=2, nx=nx, ny=20, x1=nx / 20, bc_x=bc, bc_y=bc)
+    clean = _base(prob)
+    clean[1, 0] += 0.9 * clean[0, 0]   # mostly one sign: the bounds decide
+    clean[2, 0] -= 0.9 * clean[0, 0]
+    clean[3, 0] += 1.0
+    for at in ((0, 0), (9, 10)):
+        U = clean.copy()
+        U[(comp, 0) + at] = value
+        R, fl, Lref, flref, scale = _run(f"flags component {comp} = {value} at {at} bc={bc} nx={nx}", prob, U, clean)
+        assert np.array_equal(fl, flref)
