@@ -360,7 +360,7 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
       for (int rr = 0; rr < 4 / NC; ++rr)
 #pragma unroll
         for (int c = 0; c < NC; ++c) F[rr][c] = G[rr][c] = fx[rr][c] = gy[rr][c] = 0.0;
-      double fF = 0.0, fG = 0.0, fs4[4] = {0.0, 0.0, 0.0, 0.0};
+      double fF = 0.0, fG = 0.0;
       const bool body = jr >= 0 && jr < tl.rows;
       if constexpr (CH) {
         /* lane k = row eta_k of the cell: x set back to conserved variables */
@@ -393,16 +393,20 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
           mr_face_flux<4, 0, GB == 2>(I, a, pts[0], gam, alpha, x, y, mr_stage_time(I, mode), fx[0]);
         }
         __syncthreads();
-        /* the x set's sums at once: four registers instead of sixteen held
-           through the y set's Step 1 */
+        /* the x set's sums at once, the face sums straight to LDS: one value
+           instead of eight held through the y set's Step 1 */
         {
-          double sF[4];
+          double sF[4], sx[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             sF[c] = mr2_sum(aF, F[0][c]);
-            fs4[c] = mr2_sum(aS, fx[0][c]);
+            sx[c] = mr2_sum(aS, fx[0][c]);
           }
           fF = mr2_pick(k, sF);
+          if (k < 2) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) FSM(k, c, cs) = sx[c];
+          }
         }
         /* field k of the y set (the stencil rows are still in place) */
         {
@@ -486,14 +490,20 @@ __global__ __launch_bounds__(MR_BLOCK) MR_OCC void k2_stage(const mr_inst* __res
       /* the quadratures over the rows: lane k receives component k's volume
          sums; the face sums of all components go through LDS */
       if constexpr (NC == 4) {
-        double sF[4], sG[4];
+        /* face sums: rows 0, 1 (lanes 0, 1 of a cell) the left face's, which
+           CH has written, 2, 3 the bottom face's */
+        double sF[4], sG[4], sy[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           if (!CH) sF[c] = mr2_sum(aF, F[0][c]);
           sG[c] = mr2_sum(aF, G[0][c]);
-          if (!CH) fs4[c] = mr2_sum(aS, fx[0][c]);
-          const double sy = mr2_sum(aS, gy[0][c]);
-          FSM(k, c, cs) = k < 2 ? fs4[c] : sy;   /* rows 0, 1: left face; 2, 3: bottom face */
+          const double sx = CH ? 0.0 : mr2_sum(aS, fx[0][c]);
+          sy[c] = mr2_sum(aS, gy[0][c]);
+          if (!CH) FSM(k, c, cs) = k < 2 ? sx : sy[c];
+        }
+        if (CH && k >= 2) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) FSM(k, c, cs) = sy[c];
         }
         if (!CH) fF = mr2_pick(k, sF);
         fG = mr2_pick(k, sG);
