@@ -64,7 +64,8 @@ constexpr int kKxFill = 512; /* work groups that fill the GPU (256 CUs x 2 resid
 constexpr int kKxFew = 1024; /* strips of k2_kxrcf_few that give every SIMD one wave    */
 /* A replayed graph follows the one before after 8 us or more on the GPU (14
    where the host launches graphs slower than they run): steps of grids up to
-   kManyCells cells, 0.2 ms or shorter, are replayed kManySteps at a time. */
+   kManyCells cells, 0.2 ms or shorter, are replayed kManySteps at a time.
+   Its capture adds 80 us to the 120 that creating a context takes. */
 constexpr int kManySteps = 8;
 constexpr long long kManyCells = 1 << 17;
 constexpr int kLearnW = 64;     /* learned-indicator work item: 64 columns ...       */
@@ -142,14 +143,18 @@ size_t strip_bound(const mrhweno_problem& p) {
    the caller set one, else kDefRows or less where strips of that height
    leave the GPU short of work.  A strip of h rows takes h + 2 row steps, one after
    another, so on a small grid the launch lasts as long as one strip: with a
-   work group to itself a CU does a row step in 4.35 us, two resident ones
-   take 6.6 us a step (15 and 22 characteristic-wise, the same ratio), and a
-   launch costs 10 us besides (all measured).  The height that minimises the
-   rounds of 2 x 256 groups by that rule is taken, the tallest among equals:
-   96 x 96 cells 1 row, 23 us (32 rows: 157); 331 x 257 4 rows, 49 us (159);
-   512 x 384 7 rows, 69 us (158); 1024 x 1024 24 rows, 257 us (318).  From
-   2048 strips on the rounds overlap and the height matters little, so it
-   stays. */
+   work group to itself a CU did a row step in 4.35 us, two resident ones
+   took 6.6 us a step (15 and 22 characteristic-wise, the same ratio; 4.6 and
+   7.0 with the present sums), and a launch costs 10 us besides.  The height
+   that minimises the rounds of 2 x 256 groups by that rule is taken, the
+   tallest among equals (kernel trace): 96 x 96 cells 1 row, 25 us (32 rows:
+   167); 331 x 257 7 rows, 56 us (167); 512 x 384 7 rows, 75 us (169); 1024 x
+   1024 18 rows, 286 us (345).  Among all heights timed the choice is the best
+   one at 96 x 96, within 4 % of it from 512 x 384 to 1400 x 1400, also for
+   beta on p, the characteristic-wise Step 1 and Burgers,
+   and 10 % slower at 331 x 257 (4 rows: 51 us; Burgers 2 rows, 30 for 33).
+   From 2048 strips on the rounds overlap and the height matters little, so
+   it stays. */
 int strip_rows(const std::vector<const mrhweno_problem*>& ps, int rows) {
   if (rows > 0) return rows;
   auto count = [&](int h) {

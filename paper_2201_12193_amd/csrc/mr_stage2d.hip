@@ -37,14 +37,15 @@
  * volume integral and the bottom-face flux.  The moment rows of the next
  * step are stored once both sets have read the stencil.
  *
- * What bounds it: FP64 issue.  A wave takes about 1,040 vector instructions
- * a row step (860 of them FP64; 1,280 and 890 before the sums moved to
- * matrix products, the top trace to registers and the ghost rules out of
- * the staging of strips without ghosts), two waves a SIMD at 236 VGPRs and
- * 76 KB of LDS a work group.  2048 x 2048, 56-row strips on 512 work
- * groups: 922 -> 775 us a launch (33 TFLOP/s of the 71.8 an FP64 matrix
+ * What bounds it: FP64 issue.  By the counters a wave takes 945 vector
+ * instructions a row step, 740 of them FP64 and 16 FP64 matrix products
+ * (1,300 and 900 before the factored basis of Step 1, the one-sided HLLC, the
+ * sums as matrix products, the top trace in registers and the ghost rules
+ * out of the staging of strips without ghosts), two waves a SIMD at 228
+ * VGPRs and 76 KB of LDS a work group.  2048 x 2048, 56-row strips on 512
+ * work groups: 983 -> 788 us a launch (31 TFLOP/s of the 71.8 an FP64 matrix
  * product reaches); 800 x 200 with inflow sides, 8-row strips: 109 -> 101;
- * 600 x 200 characteristic-wise: 254 -> 238.  Strips of 128 or 64 threads
+ * 600 x 200 characteristic-wise: 254 -> 235.  Strips of 128 or 64 threads
  * (30 or 14 owned columns) took 1.3 times as long: their narrower ring
  * costs more than the shorter barriers give. */
 template <int NC>

@@ -222,6 +222,7 @@ class Solver:
         return list(d)
 
     def set_launch(self, rows_2d: int, grid_2d: int = 0) -> None:
+        """Rows per work item of the 2D stage kernel (0: chosen by size) and its grid."""
         _check(self.ctx, lib().mrhweno_set_launch(self.ctx, int(rows_2d), int(grid_2d)))
 
     def autotune(self, rows=(8, 16, 32, 64, 128), grids=(0,), reps: int = 3):
