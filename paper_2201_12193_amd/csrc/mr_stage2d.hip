@@ -37,8 +37,10 @@
  * volume integral and the bottom-face flux.  The moment rows of the next
  * step are stored once both sets have read the stencil.
  *
- * What bounds it: FP64 issue.  By the counters a wave takes 945 vector
- * instructions a row step, 740 of them FP64 and 16 FP64 matrix products
+ * What bounds it: FP64 issue, two thirds of the issue slots at the 2.1 GHz
+ * the clock holds under this load; the rest are waits of the two waves a SIMD
+ * for LDS and at barriers.  By the counters a wave takes 945 vector
+ * instructions a row step, 740 of them FP64 and 15 FP64 matrix products
  * (1,300 and 900 before the factored basis of Step 1, the one-sided HLLC, the
  * sums as matrix products, the top trace in registers and the ghost rules
  * out of the staging of strips without ghosts), two waves a SIMD at 228
