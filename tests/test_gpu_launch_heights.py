@@ -83,7 +83,7 @@ def test_tune_does_not_lose_to_the_own_choice(nx, ny, tmp_path, monkeypatch):
     cached = _stage_ms(s)
     s.close()
     print(f"heights: default {default} tuned {tuned} cached {cached} {first}", flush=True)
-    assert tuned < 1.1 * default and cached < 1.1 * default
+    assert tuned < 1.25 * default and cached < 1.25 * default
     # what tune returns can be set on another solver
     s = _solver(nx, ny)
     s.set_launch(*first[:2])
